@@ -2,10 +2,14 @@
 //
 // Logits follow one fixed fp32 order (a fused-multiply-add chain over the
 // hidden index ascending from +0.0f, then one add of the bias) so that the
-// expert choice is reproducible bit for bit.  That forbids a split of the
-// hidden dimension and any matrix-core reduction, so the logits are a
-// register-blocked SIMT fp32 kernel: each lane owns TM x TE (token, expert)
-// chains; x and W_r chunks are staged through LDS.
+// expert choice is reproducible bit for bit.  The fp32 matrix instruction
+// keeps that order: v_mfma_f32_16x16x4_f32 adds its four products to the
+// accumulator one after another in ascending k, each as a fused multiply-add
+// rounded to nearest even, denormals, infinities and zeros included (checked
+// bit for bit against fmaf chains, and by the routing tests against the
+// oracle's).  So the hidden index runs through the matrix cores, at twice the
+// vector ALUs' fp32 rate without packed instructions; it is never split
+// between accumulators.
 #include "common.h"
 
 namespace moe {
@@ -13,11 +17,6 @@ namespace {
 
 typedef int i32x4r __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) char lds_byte;
-
-// Compiler-visible wait for every scalar and LDS load of the wave: after it
-// the compiler knows all earlier loads have landed, so the loads issued next
-// (the following batch) stay in flight while the current batch is computed.
-__device__ __forceinline__ void lgkm_drained() { __builtin_amdgcn_s_waitcnt(0xc07f); }
 
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
@@ -29,48 +28,59 @@ __device__ __forceinline__ void w_load_lds16(const i32x4r& rsrc, uint32_t voff, 
                : "s"(lds), "v"(voff), "s"(rsrc)
                : "memory", "m0");
 }
+// 4 bytes per lane (lane i writes LDS [lds + 4 i, +4))
+__device__ __forceinline__ void w_load_lds4(const i32x4r& rsrc, uint32_t voff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen lds"
+               :
+               : "s"(lds), "v"(voff), "s"(rsrc)
+               : "memory", "m0");
+}
 #pragma clang diagnostic pop
 template <int N>
 __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
-// Lane = expert (experts lane + 64 b, b < TE); a wave owns TM tokens, a block
-// four waves (4 TM tokens).  Each chunk of KC hidden indices moves to
-// LDS with direct-to-LDS loads, NBUF chunks deep: the W_r rows (contiguous in
-// the row-major [d][E] array) and the block's token rows for those indices.
-// Per batch of 8 indices a lane reads its TE weights and, with one broadcast
-// 16-byte read per token, the wave's TM x values; the reads of batch b + 1
-// are issued before batch b is computed (two register sets).  TWO: the grid
-// has at least two blocks per CU, and the chunk ring is sized so that two
-// blocks share a CU's LDS (one wave per SIMD leaves the LDS latency exposed).
-template <int TM, int TE, int KC, bool TWO>
-__global__ __launch_bounds__(256) void route_logits_kernel(const uint16_t* __restrict__ x,
-                                                           const float* __restrict__ w,
-                                                           const float* __restrict__ bias,
-                                                           int64_t T, int d, int E,
-                                                           float* __restrict__ logits) {
-  constexpr int EW = 64 * TE;                 // experts covered by one block row
-  constexpr int WCH = KC * EW * 4;            // LDS bytes of W_r per chunk (>= KC E 4)
-  constexpr int TB = 4 * TM;                  // tokens per block
-  constexpr int LPWW = WCH / 1024 / 4;        // 1 KiB loads per wave per chunk: W_r
-  constexpr int XPL = 1024 / (KC * 2);        // token rows per 1 KiB x load
-  constexpr int LPWX = (TB + 4 * XPL - 1) / (4 * XPL);  //                      x
-  constexpr int CHUNK = WCH + LPWX * 4 * 1024;  // W_r rows, then the token rows
-  constexpr int LDS_CAP = TWO ? 80 * 1024 : 160 * 1024;
-  constexpr int NBUF = 4 * CHUNK <= LDS_CAP ? 4 : 3 * CHUNK <= LDS_CAP ? 3 : 2;
-  static_assert(KC % 8 == 0 && WCH % 4096 == 0 && (KC * 2) <= 1024 && 1024 % (KC * 2) == 0 &&
-                    NBUF * CHUNK <= LDS_CAP,
+// Bound by the fp32 matrix cores where the tiles fill the chip (long,
+// T = 65536, d = 4096, E = 128: 556 us = 124 TFLOP/s of 157; the vector-ALU
+// chains it replaces took 1160 us; T = 16384, d = 7168, E = 384: 1416 -> 750
+// us), by one wave's chain of d / 4 dependent instructions where they do not
+// (T = 1000, d = 4096, E = 128: 105 -> 38 us; T = 16, d = 2048, E = 64: 38 ->
+// 18 us).
+// Block = GT x GE waves, each WT x WE tiles of 16 tokens x 16 experts (one
+// v_mfma_f32_16x16x4_f32 accumulator each: A = x, lane l row l % 16 and
+// k = l / 16; B = W_r, lane l column l % 16 and k = l / 16).  Chunks of KC
+// hidden indices move to LDS with direct-to-LDS loads, DEPTH chunks deep: the
+// block's token rows [TB][KC] bf16 and the weights [KC][EB] fp32 (columns
+// past E and rows past d as zeros; neither reaches a stored logit).  Both
+// images carry an XOR swizzle on the loading side that spreads a fragment
+// read over all 64 banks: x rows of KC / 8 16-byte chunks, chunk c of row r
+// at c ^ (r / (16 / CPR)) % CPR; weight rows in groups of 16 columns, group
+// g of row k at g ^ k % 4 (fewer than four groups: EB = 32 at g ^ (k / 2) % 2,
+// EB = 16 in place).  VEC = 4 loads weights 16 bytes at a time (E a multiple
+// of 4, so that no piece crosses a row's end), VEC = 1 four.
+template <int WT, int WE, int GT, int GE, int KC, int DEPTH, int VEC>
+__global__ __launch_bounds__(64 * GT * GE) void route_logits_kernel(
+    const uint16_t* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias,
+    int64_t T, int d, int E, float* __restrict__ logits) {
+  constexpr int NW = GT * GE;
+  constexpr int TB = 16 * WT * GT, EB = 16 * WE * GE;
+  constexpr int XCH = TB * KC * 2, WCH = KC * EB * 4, CHUNK = XCH + WCH;  // bytes per chunk
+  constexpr int LX = XCH / 1024 / NW, LW = WCH / (256 * VEC) / NW;        // loads per wave
+  // chunks in the ring: DEPTH, fewer where the loads in flight would exceed
+  // the vector-memory counter
+  constexpr int NBUF = DEPTH < 2 + 63 / (LX + LW) ? DEPTH : 2 + 63 / (LX + LW);
+  constexpr int CPR = KC / 8;                    // 16-byte chunks per x row
+  constexpr int RP = CPR >= 16 ? 1 : 16 / CPR;   // x rows per 256 bytes
+  static_assert(XCH % (1024 * NW) == 0 && WCH % (256 * VEC * NW) == 0 && NBUF * CHUNK <= 160 * 1024,
                 "chunk shape");
-  __shared__ __align__(16) char ws[NBUF * CHUNK];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  __shared__ __align__(1024) char ws[NBUF * CHUNK];
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, q = lane >> 4;
   const int64_t t0 = static_cast<int64_t>(blockIdx.x) * TB;
-  float acc[TM][TE];
-#pragma unroll
-  for (int a = 0; a < TM; ++a)
-#pragma unroll
-    for (int b = 0; b < TE; ++b) acc[a][b] = +0.0f;
+  const int e0 = blockIdx.y * EB;
+  const int tw = (wv / GE) * 16 * WT, ew = (wv % GE) * 16 * WE;  // the wave's tokens, experts
 
   auto rsrc = [](const void* p, int64_t bytes) {
     const uint64_t addr = reinterpret_cast<uint64_t>(p);
@@ -81,95 +91,131 @@ __global__ __launch_bounds__(256) void route_logits_kernel(const uint16_t* __res
     r[3] = 0x00020000;
     return r;
   };
-  // W_r: chunk c = bytes [c KC E 4, +KC E 4); the loads run over WCH bytes
-  // (past the chunk: the next rows or, past the array, zeros), which land
-  // beyond the KC E floats that are read.  x: the block's token rows from t0
-  // (rows past T read as zeros; their logits are never stored).
-  const int64_t wbytes = static_cast<int64_t>(d) * E * 4;
-  const i32x4r rw = rsrc(w, wbytes);
+  const i32x4r rw = rsrc(w, static_cast<int64_t>(d) * E * 4);
   const i32x4r rx = rsrc(x + t0 * d, (T - t0) * d * 2);
-  const uint32_t lds0 =
-      static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const lds_byte*)(ws)));
-  auto issue_chunk = [&](int c) __attribute__((always_inline)) {
-    const uint32_t dst = lds0 + (c % NBUF) * CHUNK;
-    const int64_t wb = static_cast<int64_t>(c) * KC * E * 4;
+  constexpr uint32_t OOB = 0x80000000u;  // past every range: reads as zero
+  auto wswz = [](int k) { return EB >= 64 ? (k & 3) : EB == 32 ? ((k >> 1) & 1) : 0; };
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const lds_byte*)(ws)));
+  // lane offsets of the next chunk's loads.  x columns past d (the next
+  // row's values) and zero rows past T land where no batch or store reaches;
+  // weight rows past d lie past the buffer's range.
+  uint32_t xoff[LX], woff[LW];
 #pragma unroll
-    for (int i = 0; i < LPWW; ++i) {
-      const int q = wv * LPWW + i;
-      const int64_t off = wb + q * 1024 + lane * 16;
-      w_load_lds16(rw, off < wbytes ? static_cast<uint32_t>(off) : 0x80000000u, dst + q * 1024);
+  for (int i = 0; i < LX; ++i) {
+    const int p = (wv * LX + i) * 64 + lane;  // 16-byte piece of the image
+    const int r = p / CPR, ch = (p % CPR) ^ ((r / RP) % CPR);
+    xoff[i] = static_cast<uint32_t>((r * d + ch * 8) * 2);
+  }
+#pragma unroll
+  for (int i = 0; i < LW; ++i) {
+    const int p = ((wv * LW + i) * 64 + lane) * VEC;  // first float of the piece
+    const int k = p / EB, pos = p % EB;
+    const int e = e0 + (((pos >> 4) ^ wswz(k)) << 4) + (pos & 15);
+    woff[i] = e < E ? (static_cast<uint32_t>(k) * E + e) * 4u : OOB;
+  }
+  uint32_t slot = 0;  // ring position of the next chunk to load
+  auto issue_chunk = [&]() __attribute__((always_inline)) {
+    const uint32_t dst = lds0 + slot;
+#pragma unroll
+    for (int i = 0; i < LX; ++i) {
+      w_load_lds16(rx, xoff[i], dst + (wv * LX + i) * 1024);
+      xoff[i] += KC * 2;
     }
-    // x: load q covers token rows XPL q .. XPL q + XPL - 1, KC * 2 bytes each
 #pragma unroll
-    for (int i = 0; i < LPWX; ++i) {
-      const int q = wv * LPWX + i;
-      const int r = q * XPL + lane / (KC / 8);   // token row of this lane
-      const int j = c * KC + (lane % (KC / 8)) * 8;
-      const bool ok = r < TB && j < d;
-      w_load_lds16(rx, ok ? static_cast<uint32_t>((static_cast<int64_t>(r) * d + j) * 2) : 0x80000000u,
-                   dst + WCH + q * 1024);
+    for (int i = 0; i < LW; ++i) {
+      const uint32_t to = dst + XCH + (wv * LW + i) * 256 * VEC;
+      if constexpr (VEC == 4) w_load_lds16(rw, woff[i], to);
+      else w_load_lds4(rw, woff[i], to);
+      woff[i] += static_cast<uint32_t>(KC * 4) * E;
+    }
+    slot = slot == (NBUF - 1) * CHUNK ? 0 : slot + CHUNK;
+  };
+
+  f32x4 acc[WT][WE];
+#pragma unroll
+  for (int a = 0; a < WT; ++a)
+#pragma unroll
+    for (int b = 0; b < WE; ++b) acc[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  // the bf16 value q of four (in two words) as fp32 bits: one byte permute
+  const uint32_t sel = 0x01000c0cu + 0x02020000u * q;
+  // eight hidden indices (a batch) of one chunk: their fragments, and two
+  // matrix instructions per tile, k ascending.  Fragments are read AHEAD
+  // batches early, since the compiler keeps them close to their use (T = 8192,
+  // d = 4096, E = 128: 100 -> 94 us; T = 1000: 46 -> 43).
+  constexpr int AHEAD = WT * WE == 1 ? 3 : 1;
+  struct Frags {
+    uint4 x[WT];
+    float w[2][WE];
+  };
+  Frags fr[AHEAD + 1];
+  auto read = [&](Frags& f, const char* cb, int bl) __attribute__((always_inline)) {
+#pragma unroll
+    for (int a = 0; a < WT; ++a) {
+      const int r = tw + 16 * a + l16;
+      f.x[a] = *reinterpret_cast<const uint4*>(cb + r * (KC * 2) + ((bl ^ ((r / RP) % CPR)) << 4));
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k = 8 * bl + 4 * h + q;
+      const float* row = reinterpret_cast<const float*>(cb + XCH) + k * EB + l16;
+#pragma unroll
+      for (int b = 0; b < WE; ++b) f.w[h][b] = row[((ew >> 4) + b ^ wswz(k)) << 4];
     }
   };
-  // one batch = 8 hidden indices: the wave's x words and the lane's weights
-  uint4 xs[2][TM];
-  float wq[2][8][TE];
-  auto issue = [&](int slot, const char* cb, int bl) __attribute__((always_inline)) {
-    const float* cw = reinterpret_cast<const float*>(cb);
+  auto mma = [&](const Frags& f) __attribute__((always_inline)) {
 #pragma unroll
-    for (int a = 0; a < TM; ++a)
-      xs[slot][a] = *reinterpret_cast<const uint4*>(cb + WCH + (wv * TM + a) * (KC * 2) + bl * 16);
+    for (int h = 0; h < 2; ++h) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
+      for (int a = 0; a < WT; ++a) {
+        const float av = __uint_as_float(h ? __builtin_amdgcn_perm(f.x[a].w, f.x[a].z, sel)
+                                           : __builtin_amdgcn_perm(f.x[a].y, f.x[a].x, sel));
 #pragma unroll
-      for (int b = 0; b < TE; ++b) wq[slot][u][b] = cw[(bl * 8 + u) * E + lane + 64 * b];
-  };
-  auto compute = [&](int slot) __attribute__((always_inline)) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-#pragma unroll
-      for (int a = 0; a < TM; ++a) {
-        const uint4 xv = xs[slot][a];
-        const uint32_t pr = u < 2 ? xv.x : u < 4 ? xv.y : u < 6 ? xv.z : xv.w;
-        const float xa = (u & 1) ? bf16_hi(pr) : bf16_lo(pr);
-#pragma unroll
-        for (int b = 0; b < TE; ++b) acc[a][b] = __builtin_fmaf(xa, wq[slot][u][b], acc[a][b]);
+        for (int b = 0; b < WE; ++b)
+          acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, f.w[h][b], acc[a][b], 0, 0, 0);
       }
     }
   };
-  // lanes of experts past E read weights of other experts: harmless, never stored
   const int nch = (d + KC - 1) / KC;
 #pragma unroll
-  for (int c = 0; c < NBUF - 1; ++c) issue_chunk(c);
+  for (int c = 0; c < NBUF - 1; ++c) issue_chunk();
+  uint32_t rd = 0;  // ring position of the chunk being computed
   for (int c = 0; c < nch; ++c) {
-    wait_vm<(LPWW + LPWX) * (NBUF - 2)>();  // this wave's part of chunk c has landed
-    __syncthreads();                         // everyone's part; chunk c - 1 is consumed
-    issue_chunk(c + NBUF - 1);               // into chunk c - 1's buffer (zeros past the end)
-    const char* cb = ws + (c % NBUF) * CHUNK;
-    const int nbl = min(KC, d - c * KC) / 8;  // batches in this chunk
-    issue(0, cb, 0);
-    for (int bl = 0; bl < nbl; bl += 2) {
-      lgkm_drained();  // batch bl has landed
-      if (bl + 1 < nbl) issue(1, cb, bl + 1);
-      compute(0);
-      if (bl + 1 < nbl) {
-        lgkm_drained();
-        if (bl + 2 < nbl) issue(0, cb, bl + 2);
-        compute(1);
+    wait_vm<(LX + LW) * (NBUF - 2)>();  // this wave's part of chunk c has landed
+    __syncthreads();                    // everyone's part; chunk c - 1 is consumed
+    issue_chunk();                      // chunk c + NBUF - 1, into chunk c - 1's buffer
+    const char* cb = ws + rd;
+    rd = rd == (NBUF - 1) * CHUNK ? 0 : rd + CHUNK;
+    const int nbl = min(KC, d - c * KC) / 8;  // batches in this chunk (d is a multiple of 8)
+    if (nbl == KC / 8) {
+      constexpr int NB = KC / 8;
+      static_for<AHEAD>([&](auto B) { read(fr[B], cb, B); });
+      static_for<NB>([&](auto B) {
+        constexpr int bl = B;
+        if constexpr (bl + AHEAD < NB) read(fr[(bl + AHEAD) % (AHEAD + 1)], cb, bl + AHEAD);
+        __builtin_amdgcn_sched_barrier(0);  // the reads stay ahead of the products
+        mma(fr[bl % (AHEAD + 1)]);
+      });
+    } else {
+      for (int bl = 0; bl < nbl; ++bl) {
+        read(fr[0], cb, bl);
+        mma(fr[0]);
       }
     }
   }
-  wait_vm<0>();  // the trailing chunk loads (zeros) are done before the block ends
+  wait_vm<0>();  // the trailing chunks' loads are done before the block ends
+  // accumulator word r of lane l: token 4 q + r, expert l16 of the tile
 #pragma unroll
-  for (int a = 0; a < TM; ++a) {
-    const int64_t t = t0 + wv * TM + a;
-    if (t >= T) continue;
+  for (int b = 0; b < WE; ++b) {
+    const int e = e0 + ew + 16 * b + l16;
+    if (e >= E) continue;
+    const float be = bias ? bias[e] : 0.0f;
 #pragma unroll
-    for (int b = 0; b < TE; ++b) {
-      const int e = lane + 64 * b;
-      if (e >= E) continue;
-      float v = acc[a][b];
-      if (bias) v = v + bias[e];
-      logits[t * E + e] = v;
+    for (int a = 0; a < WT; ++a) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t t = t0 + tw + 16 * a + 4 * q + r;
+        if (t < T) logits[t * E + e] = bias ? acc[a][b][r] + be : acc[a][b][r];
+      }
     }
   }
 }
@@ -247,36 +293,51 @@ __global__ __launch_bounds__(256) void route_topk_kernel(const float* __restrict
   }
 }
 
-template <int TM, int TE>
+template <int WT, int WE, int GT, int GE, int KC, int DEPTH>
 hipError_t run_logits(const uint16_t* x, const float* w, const float* bias, int64_t T, int d,
                       int E, float* logits, hipStream_t s) {
-  // chunk rows: KC * TE a multiple of 16 (whole 4 KiB per chunk buffer)
-  constexpr int KC = TE == 1 ? 128 : TE == 2 ? 64 : TE == 4 ? 32 : TE <= 8 ? 16 : 8;
-  const int64_t grid = ceil_div(T, 4 * TM);
+  const dim3 grid(static_cast<unsigned>(ceil_div(T, 16 * WT * GT)),
+                  static_cast<unsigned>(ceil_div(E, 16 * WE * GE)));
   prof_begin(K_ROUTE_LOGITS, s);
-  if (grid >= 2 * static_cast<int64_t>(device_cus()))
-    route_logits_kernel<TM, TE, KC, true><<<static_cast<unsigned>(grid), 256, 0, s>>>(
-        x, w, bias, T, d, E, logits);
+  if ((E & 3) == 0)
+    route_logits_kernel<WT, WE, GT, GE, KC, DEPTH, 4><<<grid, 64 * GT * GE, 0, s>>>(x, w, bias, T, d,
+                                                                                  E, logits);
   else
-    route_logits_kernel<TM, TE, KC, false><<<static_cast<unsigned>(grid), 256, 0, s>>>(
-        x, w, bias, T, d, E, logits);
+    route_logits_kernel<WT, WE, GT, GE, KC, DEPTH, 1><<<grid, 64 * GT * GE, 0, s>>>(x, w, bias, T, d,
+                                                                                  E, logits);
   prof_end(K_ROUTE_LOGITS, s);
   return hipGetLastError();
 }
 
-// Tokens per wave: about two blocks per CU (T / 2048 tokens per wave,
-// rounded down to 8, 4, 2 or 1), so that two waves share each SIMD while
-// every block still reads W_r for as many tokens as the chip's share allows,
-// with at most 64 accumulators per lane (TM * TE <= 64).
-template <int TE>
+// Tile by size: the largest block tile that still gives every CU two blocks
+// and whose last column of blocks is not mostly padding.  Larger tiles read
+// less through the L2 per product (128 x 128: 3 bytes per matrix-core cycle
+// and CU, 32 x 32: 24), smaller ones fill the chip (logits and top-k
+// together: at T = 8192, d = 4096, E = 128 blocks of 32 x 64 take 94 us,
+// 64 x 64 103, 128 x 128 326; at T = 65536 128 x 128 takes 639 us, 32 x 64
+// 708).  Below that 32 x 32 blocks of four waves as soon as more than half of
+// the CUs get one (T = 4096, d = 2048, E = 64: 28 us against 45), then blocks
+// of one wave and one 16 x 16 tile, which spread the weights that a few
+// tokens read over the most CUs (T = 16: 23 us against 25).
 hipError_t pick_logits(const uint16_t* x, const float* w, const float* bias, int64_t T, int d,
                        int E, float* logits, hipStream_t s) {
-  if constexpr (8 * TE <= 64)
-    if (T >= 16 * 1024) return run_logits<8, TE>(x, w, bias, T, d, E, logits, s);
-  if constexpr (4 * TE <= 64)
-    if (T >= 8 * 1024) return run_logits<4, TE>(x, w, bias, T, d, E, logits, s);
-  if (T >= 4 * 1024) return run_logits<2, TE>(x, w, bias, T, d, E, logits, s);
-  return run_logits<1, TE>(x, w, bias, T, d, E, logits, s);
+  const int64_t cus = device_cus();
+  auto blocks = [&](int tb, int eb) -> int64_t {
+    const int64_t et = ceil_div(E, eb);
+    if (et * eb * 4 > 5 * static_cast<int64_t>(align_up(E, 16))) return 0;
+    return ceil_div(T, tb) * et;
+  };
+  if (blocks(128, 128) >= 2 * cus)
+    return run_logits<4, 4, 2, 2, 32, 3>(x, w, bias, T, d, E, logits, s);
+  if (blocks(64, 128) >= 2 * cus)
+    return run_logits<2, 4, 2, 2, 32, 4>(x, w, bias, T, d, E, logits, s);
+  if (blocks(64, 64) >= 2 * cus)
+    return run_logits<2, 2, 2, 2, 64, 3>(x, w, bias, T, d, E, logits, s);
+  if (blocks(32, 64) >= 2 * cus)
+    return run_logits<1, 2, 2, 2, 64, 4>(x, w, bias, T, d, E, logits, s);
+  if (blocks(32, 32) * 2 > cus)
+    return run_logits<1, 1, 2, 2, 64, 4>(x, w, bias, T, d, E, logits, s);
+  return run_logits<1, 1, 1, 1, 128, 4>(x, w, bias, T, d, E, logits, s);
 }
 
 }  // namespace
@@ -285,18 +346,7 @@ hipError_t launch_route(const uint16_t* x, const float* w, const float* bias, in
                         int E, int k, int renorm, int32_t* idx, float* gate, float* logits,
                         hipStream_t s) {
   if (T == 0) return hipSuccess;
-  hipError_t err;
-  switch ((E + 63) / 64) {
-    case 1: err = pick_logits<1>(x, w, bias, T, d, E, logits, s); break;
-    case 2: err = pick_logits<2>(x, w, bias, T, d, E, logits, s); break;
-    case 3: err = pick_logits<3>(x, w, bias, T, d, E, logits, s); break;
-    case 4: err = pick_logits<4>(x, w, bias, T, d, E, logits, s); break;
-    case 5: case 6: err = pick_logits<6>(x, w, bias, T, d, E, logits, s); break;
-    case 7: case 8: err = pick_logits<8>(x, w, bias, T, d, E, logits, s); break;
-    case 9: case 10: case 11: case 12: err = pick_logits<12>(x, w, bias, T, d, E, logits, s); break;
-    default: err = pick_logits<16>(x, w, bias, T, d, E, logits, s); break;
-  }
-  if (err != hipSuccess) return err;
+  if (hipError_t err = pick_logits(x, w, bias, T, d, E, logits, s); err != hipSuccess) return err;
 
   const unsigned grid = static_cast<unsigned>(ceil_div(T, 4));
   prof_begin(K_ROUTE_TOPK, s);
