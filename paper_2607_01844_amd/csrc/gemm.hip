@@ -97,6 +97,10 @@ struct Traits {
   static constexpr bool DUAL = MODE == FWD_GATE_UP || MODE == WGRAD_GATE_UP || MODE == RT_DW;
   // grouped weight gradients (K = an expert's rows, zero tiles for empty experts)
   static constexpr bool WG = MODE == WGRAD_GATE_UP || MODE == WGRAD_DOWN;
+  // an expert's rows come in equal tiles of up to 256 rows instead of full
+  // tiles and a rest (the dense products, which have one rest in all, do not:
+  // their epilogues leave no registers for the extra loops)
+  static constexpr bool EQ_ROWS = !A_N && !DENSE;
 };
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
@@ -198,7 +202,8 @@ struct KOperand {
   int kmax0, kmax1; // valid k of source 0 / 1
   int nk0;          // steps of source 0
 
-  // MFMA fragment: 8 consecutive k (k-group `kg` of substep s) of tile row r
+  // MFMA fragment: 8 consecutive k (k-group `kg` of substep s) of row r of a
+  // block of 32 rows at `t` (the swizzle repeats every 16 rows)
   static __device__ __forceinline__ bf16x8 frag(const lds_char* t, int r, int s, int kg) {
     return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8*>(t + koff(r, 2 * s + kg));
   }
@@ -431,11 +436,22 @@ __device__ __forceinline__ uint2 pack4(float a, float b, float c, float d) {
 }
 
 
-// One output tile of one expert.
+// One output tile of one expert.  h = its height in 32-row blocks (8 unless
+// the mode takes the rows in equal tiles: tile_blocks below).
 struct Tile {
   bool valid;
-  int e, m0, n0, seg, ne, nk;
+  int e, m0, n0, seg, ne, nk, h;
 };
+
+// Height, in blocks of 32 rows, of the mt = ceil(rows / 256) tiles that `rows`
+// rows are cut into: equal tiles instead of full ones and a rest, so that
+// padding costs at most 31 rows a tile and no compute unit gets only full
+// tiles while another gets only rests.  At least two blocks (one per wave
+// row).  384 rows: two tiles of 192 (6 blocks) instead of two of 256.
+// Measured against full tiles: the four row-grouped products of 32 experts of
+// 339 rows (d = 7168, f = 2048) 2415 -> 1930 us together, of 64 experts of
+// 384 rows (d = 2048, f = 1408) 1125 -> 1060 us.
+__device__ __forceinline__ int tile_blocks(int rows, int mt) { return max(2, (rows + 32 * mt - 1) / (32 * mt)); }
 
 // The sequence of tiles one workgroup computes.  The grid has one workgroup
 // per CU; workgroup b runs on XCD b % 8 as CU slot b / 8 of that XCD.
@@ -549,6 +565,7 @@ struct TileIter {
       t.e = b;
       int tm, tn;
       tile_pos<8>(local, g.MT, g.NT, tm, tn);
+      t.h = BM / 32;
       t.m0 = tm * BM;
       t.n0 = tn * (DUAL ? BN / 2 : BN);
       t.seg = b * g.kspan;               // first contraction row of the batch
@@ -571,10 +588,11 @@ struct TileIter {
       const int local = L - ms0 * g.NT;
       int tm, tn;
       tile_pos<4>(local, mt_e, g.NT, tm, tn);
-      t.m0 = tm * BM;
-      t.n0 = tn * (DUAL ? BN / 2 : BN);
       t.seg = tb.off(lo);
       t.ne = tb.off(lo + 1) - t.seg;
+      t.h = tile_blocks(t.ne, mt_e);
+      t.m0 = tm * 32 * t.h;
+      t.n0 = tn * (DUAL ? BN / 2 : BN);
       const int K = (MODE == FWD_GATE_UP || MODE == DGRAD_DOWN) ? g.d : g.f;
       t.nk = ((K + BK - 1) / BK) * (MODE == DGRAD_GATE_UP ? 2 : 1);
       t.valid = true;
@@ -597,6 +615,7 @@ struct TileIter {
       const int local = L - unit * tb.nz(e);
       int tm, tn;
       tile_pos<8>(local, g.MT, g.NT, tm, tn);
+      t.h = BM / 32;
       t.m0 = tm * BM;
       t.n0 = tn * (DUAL ? BN / 2 : BN);
       t.seg = tb.off(e);
@@ -616,6 +635,7 @@ struct TileIter {
         t.m0 = (local % g.MT) * BM;
         t.n0 = (local / g.MT) * (DUAL ? BN / 2 : BN);
         t.seg = tb.off(e);
+        t.h = BM / 32;
         t.ne = 0;
         t.nk = 0;
         t.valid = true;
@@ -640,9 +660,11 @@ __global__ __launch_bounds__(NTHR, 1) void grouped_gemm_kernel(GemmArgs g) {
   const int64_t wdf = static_cast<int64_t>(d) * f;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = w & 1, wn = w >> 1;  // 2 x 4 waves, each 128 rows x 64 columns
-  const int l32 = lane & 31, lh = lane >> 5;
-
+  // 2 x 4 waves, each up to 128 rows x 64 columns.  Equal-row modes put both
+  // wave rows on every SIMD (waves w and w + 4 share one), so that the rows
+  // of a tile of an odd number of blocks are still shared evenly.
+  constexpr bool EQ_ROWS = Traits<MODE>::EQ_ROWS;
+  const int wm = EQ_ROWS ? (w ^ (w >> 2)) & 1 : w & 1, wn = w >> 1;
   // ------------------------------------------------------- operand setup
   // A side = rows m of the output, B side = columns n of the output.
   auto setupA = [&](const Tile& tl, AOp& A) __attribute__((always_inline)) {
@@ -650,20 +672,20 @@ __global__ __launch_bounds__(NTHR, 1) void grouped_gemm_kernel(GemmArgs g) {
     if constexpr (MODE == FWD_GATE_UP) {
       const uint16_t* xa = g.x_perm + (int64_t)(seg + m0) * d;
       A.rsrc0 = A.rsrc1 = make_rsrc(xa, (int64_t)(ne - m0) * d * 2);
-      A.ld = d * 2; A.rows = ne - m0; A.kmax0 = A.kmax1 = d; A.nk0 = (d + BK - 1) / BK;
+      A.ld = d * 2; A.rows = min(ne - m0, 32 * tl.h); A.kmax0 = A.kmax1 = d; A.nk0 = (d + BK - 1) / BK;
     } else if constexpr (MODE == FWD_DOWN) {
       const uint16_t* aa = g.act_in + (int64_t)(seg + m0) * f;
       A.rsrc0 = A.rsrc1 = make_rsrc(aa, (int64_t)(ne - m0) * f * 2);
-      A.ld = f * 2; A.rows = ne - m0; A.kmax0 = A.kmax1 = f; A.nk0 = (f + BK - 1) / BK;
+      A.ld = f * 2; A.rows = min(ne - m0, 32 * tl.h); A.kmax0 = A.kmax1 = f; A.nk0 = (f + BK - 1) / BK;
     } else if constexpr (MODE == DGRAD_DOWN) {
       const uint16_t* ya = g.dy + (int64_t)(seg + m0) * d;
       A.rsrc0 = A.rsrc1 = make_rsrc(ya, (int64_t)(ne - m0) * d * 2);
-      A.ld = d * 2; A.rows = ne - m0; A.kmax0 = A.kmax1 = d; A.nk0 = (d + BK - 1) / BK;
+      A.ld = d * 2; A.rows = min(ne - m0, 32 * tl.h); A.kmax0 = A.kmax1 = d; A.nk0 = (d + BK - 1) / BK;
     } else if constexpr (MODE == DGRAD_GATE_UP) {
       const int64_t ro = (int64_t)(seg + m0) * f;
       A.rsrc0 = make_rsrc(g.dhg_in + ro, (int64_t)(ne - m0) * f * 2);
       A.rsrc1 = make_rsrc(g.dhu_in + ro, (int64_t)(ne - m0) * f * 2);
-      A.ld = f * 2; A.rows = ne - m0; A.kmax0 = A.kmax1 = f; A.nk0 = (f + BK - 1) / BK;
+      A.ld = f * 2; A.rows = min(ne - m0, 32 * tl.h); A.kmax0 = A.kmax1 = f; A.nk0 = (f + BK - 1) / BK;
     } else if constexpr (MODE == WGRAD_GATE_UP) {
       A.ptr0 = g.x_perm + (int64_t)seg * d + m0; A.range0 = ((int64_t)ne * d - m0) * 2;
       A.ptr1 = A.ptr0 + 128; A.range1 = A.range0 - 256;
@@ -740,11 +762,12 @@ __global__ __launch_bounds__(NTHR, 1) void grouped_gemm_kernel(GemmArgs g) {
     }
   };
 
-  // First tile row of each 32-row MFMA block: four on the A side, two on
-  // the B side (dual: the gate and the up column block of the same f).
-  int arow[4], brow[2];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) arow[i] = wm * 128 + 32 * i;
+  // First tile row of the wave's 32-row MFMA blocks: arow0 + 32 i, i < 4, on
+  // the A side; two blocks on the B side (dual: the gate and the up column
+  // block of the same f).
+  // Equal-row tiles give the first wave row (h + 1) / 2 blocks and the second
+  // the rest: arow0 is set tile by tile.
+  int arow0 = wm * 128, brow[2];
 #pragma unroll
   for (int jj = 0; jj < 2; ++jj) brow[jj] = DUAL ? jj * (BN / 2) + wn * 32 : wn * 64 + 32 * jj;
 
@@ -759,7 +782,7 @@ __global__ __launch_bounds__(NTHR, 1) void grouped_gemm_kernel(GemmArgs g) {
   };
 
   // ------------------------------------------------------------ epilogue
-  // acc[i][j][4q + u]: output row m = arow[i] + l32 (tile-relative),
+  // acc[i][j][4q + u]: output row m = arow0 + 32 i + l32 (tile-relative),
   // output column n = brow[j] + 8q + 4*lh + u.  Each wave passes its
   // 128 x 64 block through its own 4 KiB LDS patch, 32 rows (16 in fp32) at
   // a time: it writes the accumulators in the MFMA layout and reads them
@@ -767,15 +790,16 @@ __global__ __launch_bounds__(NTHR, 1) void grouped_gemm_kernel(GemmArgs g) {
   // 4 or 8 lanes cover one contiguous row segment (whole 64- or 128-byte
   // pieces instead of 32 scattered 8-byte pieces per instruction).  Patch
   // chunks carry XOR swizzles that keep the 64 banks conflict-free.
-  auto epilogue = [&](const Tile& tl, lds_char* patch) __attribute__((always_inline)) {
+  auto epilogue = [&](const Tile& tl, int ai, lds_char* patch) __attribute__((always_inline)) {
     const int e = tl.e, m0 = tl.m0, n0 = tl.n0, seg = tl.seg, ne = tl.ne;
     // lane-derived indices recomputed here (not hoisted and kept live
     // across the K loop, where they would be spilled)
     const int lane = opaque(threadIdx.x & 63);
     const int l32 = lane & 31, lh = lane >> 5;
-    const int mvalid = DENSE   ? (g.dM - m0)
-                       : WGRAD ? ((MODE == WGRAD_GATE_UP ? d : f) - m0)
-                               : (ne - m0);
+    const int mrows = DENSE   ? (g.dM - m0)
+                      : WGRAD ? ((MODE == WGRAD_GATE_UP ? d : f) - m0)
+                              : (ne - m0);
+    const int mvalid = EQ_ROWS ? min(mrows, 32 * tl.h) : mrows;
     typedef uint32_t u32x2v __attribute__((ext_vector_type(2)));
     typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
     typedef float f32x4v __attribute__((ext_vector_type(4)));
@@ -800,7 +824,8 @@ __global__ __launch_bounds__(NTHR, 1) void grouped_gemm_kernel(GemmArgs g) {
     };
     static_for<4>([&](auto I) {
       constexpr int i = I;
-      const int rb = wm * 128 + 32 * i;  // tile row of the block's first row
+      if (i >= ai) return;
+      const int rb = arow0 + 32 * i;  // tile row of the block's first row
       if (rb >= mvalid) return;
       if constexpr (MODE == FWD_GATE_UP || MODE == WGRAD_GATE_UP) {
         // gate [32][32] bf16 at +0, up at +2048; 64-byte rows, 16-byte chunk c
@@ -1154,7 +1179,7 @@ __global__ __launch_bounds__(NTHR, 1) void grouped_gemm_kernel(GemmArgs g) {
         const lds_char* ta = ring + sa * UNIT + (sub >> 1) * HALF;
         const lds_char* tbl = ring + (NA + sb) * UNIT + (sub >> 1) * HALF;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) F.a[i] = AOp::frag(ta, arow[i], sub & 1, lane);
+        for (int i = 0; i < 4; ++i) F.a[i] = AOp::frag(ta, arow0 + 32 * i, sub & 1, lane);
 #pragma unroll
         for (int jj = 0; jj < 2; ++jj) F.b[jj] = BOp::frag(tbl, brow[jj], sub & 1, lane);
       };
@@ -1475,41 +1500,27 @@ __global__ __launch_bounds__(NTHR, 1) void grouped_gemm_kernel(GemmArgs g) {
     struct Frags {
       bf16x8 a[4], b[2];
     };
-    // fragments of sub-step `sub` (16 k, 0..3) of the step held in A's ring
-    // slot `sa` and B's ring slot `sb`
-    auto load_frags = [&](Frags& F, int sa, int sb, int sub) __attribute__((always_inline)) {
-      const lds_char* ta = ring + sa * UNIT + (A_N ? (sub >> 1) * HALF : 0);
-      const lds_char* tb = ring + (NA + sb) * UNIT + (B_N ? (sub >> 1) * HALF : 0);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        if constexpr (A_N) F.a[i] = AOp::frag(ta, arow[i], sub & 1, lane);
-        else F.a[i] = AOp::frag(ta, arow[i] + l32, sub, lh);
-      }
-#pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
-        if constexpr (B_K) F.b[jj] = BOp::frag(tb, brow[jj] + l32, sub, lh);
-        else F.b[jj] = BOp::frag(tb, brow[jj], sub & 1, lane);
-      }
-    };
-    // one fragment f of sub-step `sub` (f = 0..3: A's row blocks, 4..5: B's)
+    int fl = lane;  // the lane, made opaque tile by tile (k_loop): addresses of one
+                    // row-block count are not kept live through another's loop
+    // one fragment f of sub-step `sub` (16 k, 0..3) of the step held in A's
+    // ring slot `sa` and B's ring slot `sb` (f = 0..3: A's row blocks, 4..5: B's)
     auto load_frag1 = [&](Frags& F, int sa, int sb, int sub, auto FI) __attribute__((always_inline)) {
       constexpr int f = FI;
       if constexpr (f < 4) {
         const lds_char* ta = ring + sa * UNIT + (A_N ? (sub >> 1) * HALF : 0);
-        if constexpr (A_N) F.a[f] = AOp::frag(ta, arow[f], sub & 1, lane);
-        else F.a[f] = AOp::frag(ta, arow[f] + l32, sub, lh);
+        if constexpr (A_N) F.a[f] = AOp::frag(ta, arow0 + 32 * f, sub & 1, fl);
+        else F.a[f] = AOp::frag(ta + (arow0 + 32 * f) * (BK * 2), fl & 31, sub, fl >> 5);
       } else {
         const lds_char* tb = ring + (NA + sb) * UNIT + (B_N ? (sub >> 1) * HALF : 0);
-        if constexpr (B_K) F.b[f - 4] = BOp::frag(tb, brow[f - 4] + l32, sub, lh);
-        else F.b[f - 4] = BOp::frag(tb, brow[f - 4], sub & 1, lane);
+        if constexpr (B_K) F.b[f - 4] = BOp::frag(tb + (brow[0] + 32 * (f - 4)) * (BK * 2), fl & 31, sub, fl >> 5);
+        else F.b[f - 4] = BOp::frag(tb, brow[f - 4], sub & 1, fl);
       }
     };
-    auto mma = [&](const Frags& F) __attribute__((always_inline)) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
-          acc[i][jj] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(F.b[jj], F.a[i], acc[i][jj], 0, 0, 0);
+    // all fragments of a sub-step: AI row blocks of A, two column blocks of B
+    auto load_frags = [&](Frags& F, int sa, int sb, int sub, auto AIC) __attribute__((always_inline)) {
+      static_for<6>([&](auto FI) {
+        if constexpr (FI >= 4 || FI < AIC) load_frag1(F, sa, sb, sub, FI);
+      });
     };
 
     // ---------------------------------------------------------- tile stream
@@ -1591,25 +1602,28 @@ __global__ __launch_bounds__(NTHR, 1) void grouped_gemm_kernel(GemmArgs g) {
 
       Frags cur, nxt;
       int ra = 0, rb = 0;  // ring slots (A: 0..1, B: 0..2) of the step being computed
-      load_frags(cur, 0, 0, 0);
       auto sync = [&]() __attribute__((always_inline)) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // this wave's fragment reads are done
       };
-      // the 8 MFMAs of one sub-step on F, with the six fragment reads of the
-      // next sub-step (into G) between the first three, in the order the next
-      // sub-step's MFMAs need them (a0 b0 | b1 a1 | a2 a3), so that each has
-      // five or more MFMAs to arrive
-      auto mma_read = [&](const Frags& F, Frags& G, int sa, int sb, int sub) __attribute__((always_inline)) {
-        static_for<8>([&](auto T) {
+      // the 2 AI MFMAs of one sub-step on F, with the AI + 2 fragment reads of
+      // the next sub-step (into G) after the first of them, in the order the
+      // next sub-step's MFMAs need them (a0 b0 b1 a1 a2 a3; one a MFMA, two
+      // where a single row block has only two MFMAs)
+      auto mma_read = [&](const Frags& F, Frags& G, int sa, int sb, int sub, auto AIC) __attribute__((always_inline)) {
+        constexpr int AI = AIC, per = AI == 1 ? 2 : 1;
+        static_for<2 * AI>([&](auto T) {
           constexpr int t = T;
           acc[t / 2][t % 2] =
               __builtin_amdgcn_mfma_f32_32x32x16_bf16(F.b[t % 2], F.a[t / 2], acc[t / 2][t % 2], 0, 0, 0);
           __builtin_amdgcn_sched_barrier(0);
-          if constexpr (t < 6) {
-            constexpr int f0 = t == 0 ? 0 : t == 1 ? 4 : t == 2 ? 5 : t == 3 ? 1 : t == 4 ? 2 : 3;
-            load_frag1(G, sa, sb, sub, std::integral_constant<int, f0>{});
-            __builtin_amdgcn_sched_barrier(0);
-          }
+          static_for<per>([&](auto P) {
+            constexpr int r = per * t + P;
+            if constexpr (r < AI + 2) {
+              constexpr int f0 = r == 0 ? 0 : r == 1 ? 4 : r == 2 ? 5 : r - 2;
+              load_frag1(G, sa, sb, sub, std::integral_constant<int, f0>{});
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          });
         });
       };
       while (true) {
@@ -1641,13 +1655,15 @@ __global__ __launch_bounds__(NTHR, 1) void grouped_gemm_kernel(GemmArgs g) {
         };
         // One K step.  TAIL: its look-ahead loads may reach past the tile
         // (the next tile or nothing); otherwise they stay inside it.  LAST:
-        // the tile's last step (B's refill waits for the epilogue).
-        auto step = [&](int ks, auto TAIL, auto LAST) __attribute__((always_inline)) {
+        // the tile's last step (B's refill waits for the epilogue).  AI: the
+        // wave's row blocks in this tile.
+        auto step = [&](int ks, auto AIC, auto TAIL, auto LAST) __attribute__((always_inline)) {
           constexpr bool tail = TAIL, last = LAST;
+          constexpr int AI = AIC;
           const int ra1 = ra ^ 1, rb1 = rb == 2 ? 0 : rb + 1;  // slots of the next step
-          mma_read(cur, nxt, ra, rb, 1);
-          mma_read(nxt, cur, ra, rb, 2);
-          mma_read(cur, nxt, ra, rb, 3);
+          mma_read(cur, nxt, ra, rb, 1, AIC);
+          mma_read(nxt, cur, ra, rb, 2, AIC);
+          mma_read(cur, nxt, ra, rb, 3, AIC);
           sync();
           wait_vmcnt<X_END>();
           __builtin_amdgcn_s_barrier();
@@ -1656,52 +1672,79 @@ __global__ __launch_bounds__(NTHR, 1) void grouped_gemm_kernel(GemmArgs g) {
           // ks + 3 (deferred past the epilogue on the tile's last step)
           if constexpr (!last) {
             lgkm_drained();
-            load_frags(cur, ra1, rb1, 0);
+            load_frags(cur, ra1, rb1, 0, AIC);
             __builtin_amdgcn_sched_barrier(0);
-            // the 8 MFMAs of sub-step 3 with the loads between them (A's parts
-            // after the second and fourth, B's after the sixth and eighth)
-            static_for<8>([&](auto T) {
+            // the 2 AI MFMAs of sub-step 3 with the four parts of the loads
+            // (A's, then B's) spread evenly between them
+            static_for<2 * AI>([&](auto T) {
               constexpr int t = T;
               acc[t / 2][t % 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                   nxt.b[t % 2], nxt.a[t / 2], acc[t / 2][t % 2], 0, 0, 0);
               __builtin_amdgcn_sched_barrier(0);
-              if constexpr (t % 2 == 1) {
-                if constexpr (t < 4) {
-                  if constexpr (tail) loadA(ks + 2, ra, t / 2);
-                  else issA(sa, ks + 2, ra, t / 2);
-                } else {
-                  if constexpr (tail) loadB(ks + 3, rb, t / 2 - 2);
-                  else issB(sb, ks + 3, rb, t / 2 - 2);
+              static_for<4>([&](auto P) {
+                constexpr int p = P;
+                if constexpr ((2 * p + 1) * 2 * AI / 8 == t) {
+                  if constexpr (p < 2) {
+                    if constexpr (tail) loadA(ks + 2, ra, p);
+                    else issA(sa, ks + 2, ra, p);
+                  } else {
+                    if constexpr (tail) loadB(ks + 3, rb, p - 2);
+                    else issB(sb, ks + 3, rb, p - 2);
+                  }
+                  __builtin_amdgcn_sched_barrier(0);
                 }
-                __builtin_amdgcn_sched_barrier(0);
-              }
+              });
             });
             lgkm_drained();
           } else {
             loadA(ks + 2, ra, 0);
             loadA(ks + 2, ra, 1);
             __builtin_amdgcn_sched_barrier(0);
-            mma(nxt);
+            static_for<2 * AI>([&](auto T) {
+              constexpr int t = T;
+              acc[t / 2][t % 2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                  nxt.b[t % 2], nxt.a[t / 2], acc[t / 2][t % 2], 0, 0, 0);
+            });
           }
           __builtin_amdgcn_sched_barrier(0);
           ra = ra1;
           rb = rb1;
         };
-        int ks = 0;
-        // steps whose loads stay inside the tile
-        for (; ks + NB < nk; ++ks) step(ks, std::false_type{}, std::false_type{});
-        // the last steps reach into the next tile: prepare its loads now
-        tn = it.next(g, tb);
-        if (tn.valid) {
-          prep(tn, xa, xb);
-          nkn = tn.nk;
+        // the tile's K loop with this wave's number of row blocks (the waves of
+        // the two wave rows may differ by one; all pass the same barriers)
+        auto k_loop = [&](auto AIC) __attribute__((always_inline)) {
+          fl = opaque(threadIdx.x & 63);
+          lgkm_drained();
+          load_frags(cur, ra, rb, 0, AIC);
+          int ks = 0;
+          // steps whose loads stay inside the tile
+          for (; ks + NB < nk; ++ks) step(ks, AIC, std::false_type{}, std::false_type{});
+          // the last steps reach into the next tile: prepare its loads now
+          tn = it.next(g, tb);
+          if (tn.valid) {
+            prep(tn, xa, xb);
+            nkn = tn.nk;
+          }
+          for (; ks + 1 < nk; ++ks) step(ks, AIC, std::true_type{}, std::false_type{});
+          step(ks, AIC, std::true_type{}, std::true_type{});
+        };
+        int ai = 4;
+        if constexpr (EQ_ROWS) {
+          ai = wm == 0 ? (tc.h + 1) >> 1 : tc.h >> 1;
+          arow0 = wm == 0 ? 0 : 32 * ((tc.h + 1) >> 1);
+          switch (ai) {
+            case 1: k_loop(std::integral_constant<int, 1>{}); break;
+            case 2: k_loop(std::integral_constant<int, 2>{}); break;
+            case 3: k_loop(std::integral_constant<int, 3>{}); break;
+            default: k_loop(std::integral_constant<int, 4>{}); break;
+          }
+        } else {
+          k_loop(std::integral_constant<int, 4>{});
         }
-        for (; ks + 1 < nk; ++ks) step(ks, std::true_type{}, std::false_type{});
-        step(ks, std::true_type{}, std::true_type{});
         // epilogue patches: B's slot of the tile's last step
         const int rlast = rb == 0 ? 2 : rb - 1;
         lds_char* const patch = ring + (NA + rlast) * UNIT + w * PATCH_BYTES;
-        epilogue(tc, patch);
+        epilogue(tc, ai, patch);
         zero_acc();
         // the patch reads are done once the LDS counter drains; the stores stay
         // in flight.  The next sync's vector-memory wait covers them: the
@@ -1741,8 +1784,6 @@ __global__ __launch_bounds__(NTHR, 1) void grouped_gemm_kernel(GemmArgs g) {
           __builtin_amdgcn_s_barrier();
           __builtin_amdgcn_sched_barrier(0);
         }
-        lgkm_drained();
-        load_frags(cur, ra, rb, 0);
       }
       // the last steps' out-of-range loads still write their (zero) slots:
       // let them land before the workgroup's LDS is released
