@@ -19,7 +19,9 @@ COUNTS = {
 
 
 @pytest.mark.parametrize("name", list(COUNTS))
-@pytest.mark.parametrize("d,f", [(72, 136), (264, 328)])
+# the 128-row tile (few tiles in all), and with f = 5128 the 256-row tile
+# (more than two tiles per compute unit)
+@pytest.mark.parametrize("d,f", [(72, 136), (264, 328), (72, 5128)])
 def test_rows_around_tile_heights(name, d, f):
     from paper_2607_01844_amd import moe
     counts = COUNTS[name]
