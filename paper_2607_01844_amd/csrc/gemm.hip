@@ -135,7 +135,8 @@ hipError_t launch_ffn_fwd(const uint16_t* x_perm, const int32_t* offsets, int E_
   const int64_t rt = row_tiles(cap, E_loc);
   const bool small = use_small(rt * std::max(ceil_div(f, TILE / 2), ceil_div(d, TILE)), cap, E_loc);
   const int S = small ? TILE_S : TILE;
-  if (hipError_t e = sched(offsets, E_loc, S, w, s); e != hipSuccess) return e;
+  if (small && E_loc <= REG_EXPERTS) w.mt_start = nullptr;  // the kernels form the tables
+  else if (hipError_t e = sched(offsets, E_loc, S, w, s); e != hipSuccess) return e;
   GemmArgs a{};
   a.x_perm = x_perm; a.wg = wg; a.wu = wu; a.wd = wd;
   a.offsets = offsets; a.mt_start = w.mt_start; a.wk_start = w.wk_start; a.nz_start = w.nz_start;
@@ -157,7 +158,14 @@ hipError_t launch_ffn_bwd(const uint16_t* dy, const uint16_t* x_perm, const uint
   const int64_t rt = row_tiles(cap, E_loc);
   const bool small = use_small(rt * std::max(ceil_div(f, TILE), ceil_div(d, TILE)), cap, E_loc);
   const int S = small ? TILE_S : TILE;
-  if (hipError_t e = sched(offsets, E_loc, S, w, s); e != hipSuccess) return e;
+  const int64_t experts = std::min<int64_t>(cap, E_loc);
+  const bool wgrad = (flags & MOE_BWD_WGRAD) != 0;
+  const bool small_g = use_small(experts * ceil_div(d, TILE) * ceil_div(f, TILE / 2), cap, E_loc);
+  const bool small_d = use_small(experts * ceil_div(f, TILE) * ceil_div(d, TILE), cap, E_loc);
+  if (small && (!wgrad || (small_g && small_d)) && E_loc <= REG_EXPERTS)
+    w.mt_start = nullptr;  // the kernels form the tables
+  else if (hipError_t e = sched(offsets, E_loc, S, w, s); e != hipSuccess)
+    return e;
   GemmArgs a{};
   a.x_perm = x_perm; a.wg = wg; a.wu = wu; a.wd = wd;
   a.hg_in = hg; a.hu_in = hu; a.dy = dy;
@@ -175,16 +183,13 @@ hipError_t launch_ffn_bwd(const uint16_t* dy, const uint16_t* x_perm, const uint
         e != hipSuccess)
       return e;
   }
-  if (flags & MOE_BWD_WGRAD) {
-    const int64_t experts = std::min<int64_t>(cap, E_loc);
-    const bool small_g = use_small(experts * ceil_div(d, TILE) * ceil_div(f, TILE / 2), cap, E_loc);
+  if (wgrad) {
     const int Sg = small_g ? TILE_S : TILE;
     a.MT = static_cast<int>(ceil_div(d, Sg));
     a.NT = static_cast<int>(ceil_div(f, Sg / 2));
     if (hipError_t e = run_gemm<WGRAD_GATE_UP>(a, small_g, K_GEMM_WGRAD_GATE_UP, s);
         e != hipSuccess)
       return e;
-    const bool small_d = use_small(experts * ceil_div(f, TILE) * ceil_div(d, TILE), cap, E_loc);
     const int Sd = small_d ? TILE_S : TILE;
     a.MT = static_cast<int>(ceil_div(f, Sd));
     a.NT = static_cast<int>(ceil_div(d, Sd));

@@ -496,15 +496,44 @@ __device__ __forceinline__ int sld(const int32_t* p) {
   asm volatile("s_load_dword %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(p) : "memory");
   return v;
 }
+// The 128-row tile's launches with up to 63 experts have no tables (mt_start
+// null): each wave forms them from the offsets with one load and a wave scan,
+// lane i holding entry i, which spares such short launches the schedule
+// kernel before them and a chain of scalar loads per tile.
+constexpr int REG_EXPERTS = 63;
+template <int S>
 struct Tables {
   const int32_t* mt_start_;  // [E_loc + 1]
   const int32_t* offsets_;   // [E_loc + 1]
   const int32_t* wk_start_;  // [E_loc + 1]
   const int32_t* nz_start_;  // [E_loc + 1]
-  __device__ __forceinline__ int mt(int i) const { return sld(mt_start_ + i); }
-  __device__ __forceinline__ int off(int i) const { return sld(offsets_ + i); }
-  __device__ __forceinline__ int wk(int i) const { return sld(wk_start_ + i); }
-  __device__ __forceinline__ int nz(int i) const { return sld(nz_start_ + i); }
+  int mt_, off_, wk_, nz_;   // entry `lane` of each (no tables)
+  __device__ __forceinline__ bool regs() const { return S == TILE_S && mt_start_ == nullptr; }
+  static __device__ __forceinline__ int lane_of(int v, int i) {
+    return __builtin_amdgcn_readlane(v, __builtin_amdgcn_readfirstlane(i));
+  }
+  __device__ __forceinline__ int mt(int i) const { return regs() ? lane_of(mt_, i) : sld(mt_start_ + i); }
+  __device__ __forceinline__ int off(int i) const { return regs() ? lane_of(off_, i) : sld(offsets_ + i); }
+  __device__ __forceinline__ int wk(int i) const { return regs() ? lane_of(wk_, i) : sld(wk_start_ + i); }
+  __device__ __forceinline__ int nz(int i) const { return regs() ? lane_of(nz_, i) : sld(nz_start_ + i); }
+  __device__ __forceinline__ void init(int E_loc, int lane) {
+    if (!regs()) return;
+    off_ = offsets_[min(lane, E_loc)];
+    const int n = offsets_[min(lane + 1, E_loc)] - off_;
+    const int v[3] = {(n + S - 1) / S, (n + BK - 1) / BK, n > 0 ? 1 : 0};
+    int incl[3] = {v[0], v[1], v[2]};
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        const int u = __shfl_up(incl[c], o, 64);
+        if (lane >= o) incl[c] += u;
+      }
+    }
+    mt_ = incl[0] - v[0];
+    wk_ = incl[1] - v[1];
+    nz_ = incl[2] - v[2];
+  }
 };
 
 // Position (m, n) of tile `local` of an mt x nt grid, walked in groups of
@@ -539,7 +568,7 @@ struct TileIter {
   bool zeros;      // weight gradients: visit only the tiles of experts without rows
 
   // Weight gradients: first tile whose K-step work starts at or after `b`.
-  __device__ __forceinline__ int wg_tile_at(const GemmArgs& g, const Tables& tb, int64_t b) const {
+  __device__ __forceinline__ int wg_tile_at(const GemmArgs& g, const Tables<S>& tb, int64_t b) const {
     const int64_t W = static_cast<int64_t>(unit) * tb.wk(g.E_loc);
     if (b >= W) return unit * tb.nz(g.E_loc);
     int lo = 0, hi = g.E_loc - 1;  // smallest e with unit * wk(e + 1) > b
@@ -552,7 +581,7 @@ struct TileIter {
     return unit * tb.nz(lo) + static_cast<int>((b - w0 + nk - 1) / nk);
   }
 
-  __device__ __forceinline__ void init(const GemmArgs& g, const Tables& tb, bool zero_tiles = false) {
+  __device__ __forceinline__ void init(const GemmArgs& g, const Tables<S>& tb, bool zero_tiles = false) {
     zeros = zero_tiles;
     cpx = gridDim.x / NXCD;
     xcd = blockIdx.x % NXCD;
@@ -578,7 +607,7 @@ struct TileIter {
       end = wg_tile_at(g, tb, W * (xcd + 1) / NXCD);
     }
   }
-  __device__ __forceinline__ Tile next(const GemmArgs& g, const Tables& tb) {
+  __device__ __forceinline__ Tile next(const GemmArgs& g, const Tables<S>& tb) {
     Tile t;
     t.valid = false;
     if constexpr (DENSE) {
@@ -1173,7 +1202,8 @@ __global__ __launch_bounds__(Geom<S>::NTHR, 2) void grouped_gemm_kernel(GemmArgs
     }
   };
 
-  const Tables tb{g.mt_start, g.offsets, g.wk_start, g.nz_start};
+  Tables<S> tb{g.mt_start, g.offsets, g.wk_start, g.nz_start};
+  if constexpr (!DENSE) tb.init(g.E_loc, lane);
   // Schedule choice (uniform over the launch).  The weight gradients
   // (grouped, and the vocabulary's dW) read both operands with transposing
   // LDS reads; when their tiles are long (at least 16 K steps on average)
