@@ -9,6 +9,7 @@ the library is not built this module raises on import; there is no fallback.
 from __future__ import annotations
 
 import ctypes
+import functools
 
 import torch
 
@@ -26,14 +27,32 @@ def _check(status: int, fn: str):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+# The host side of a call counts for small layers (a dozen calls a step): the
+# raw stream handle comes without building a Stream object each time (2.5 us
+# a call), and workspace sizes, pure functions of the call's sizes, are
+# queried once per set of sizes.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+    lambda index: torch.cuda.current_stream(index).cuda_stream)
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return _raw_stream(torch.cuda.current_device())
+
+
+@functools.lru_cache(maxsize=512, typed=True)
+def _ws_bytes(query: str, *sizes) -> int:
+    n = ctypes.c_size_t()
+    _check(getattr(lib, query)(*sizes, ctypes.byref(n)), query)
+    return n.value
 
 
 def _need(t, dtype, name, dim=None):
+    if t is not None and t.dtype is dtype and t.is_cuda and t.is_contiguous() and (
+            dim is None or t.dim() == dim):
+        return t
     if t is None:
         raise ValueError(f"{name} is required")
     if t.dtype != dtype:
@@ -42,9 +61,7 @@ def _need(t, dtype, name, dim=None):
         raise TypeError(f"{name} must be a device tensor")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if dim is not None and t.dim() != dim:
-        raise ValueError(f"{name}: expected {dim} dims, got {t.dim()}")
-    return t
+    raise ValueError(f"{name}: expected {dim} dims, got {t.dim()}")
 
 
 _ws_cache: dict = {}
@@ -57,8 +74,8 @@ def workspace(nbytes: int, device, tag: str) -> torch.Tensor:
     streams get different buffers.  A buffer replaced by a larger one is
     kept alive until the process ends, so a HIP graph captured with it never
     replays into freed memory (capture with the sizes it will replay)."""
-    stream = torch.cuda.current_stream(device).cuda_stream
-    key = (str(device), stream, tag)
+    index = device.index if device.index is not None else torch.cuda.current_device()
+    key = (index, _raw_stream(index), tag)
     buf = _ws_cache.get(key)
     if buf is None or buf.numel() < nbytes:
         if buf is not None:
@@ -84,9 +101,7 @@ def moe_route(x, w_router, router_bias, k, renorm=0, logits=None, topk_idx=None,
         topk_gate = torch.empty((T, k), dtype=torch.float32, device=dev)
     ws, nws = None, 0
     if logits is None:
-        n = ctypes.c_size_t()
-        _check(lib.moe_route_workspace_bytes(T, E, ctypes.byref(n)), "moe_route_workspace_bytes")
-        ws = workspace(n.value, dev, "route")
+        ws = workspace(_ws_bytes("moe_route_workspace_bytes", T, E), dev, "route")
         nws = ws.numel()
     else:
         _need(logits, torch.float32, "logits", 2)
@@ -123,10 +138,7 @@ def moe_route_bwd(x, w_router, logits, topk_idx, topk_gate, dgate, renorm=0, dx=
     else:
         _need(dw_router, torch.float32, "dw_router", 2)
     dbias = torch.empty((E,), dtype=torch.float32, device=dev) if with_dbias else None
-    n = ctypes.c_size_t()
-    _check(lib.moe_route_bwd_workspace_bytes(T, d, E, ctypes.byref(n)),
-           "moe_route_bwd_workspace_bytes")
-    ws = workspace(n.value, dev, "route_bwd")
+    ws = workspace(_ws_bytes("moe_route_bwd_workspace_bytes", T, d, E), dev, "route_bwd")
     _check(lib.moe_route_bwd(_ptr(x), _ptr(w_router), _ptr(logits), _ptr(topk_idx),
                              _ptr(topk_gate), _ptr(dgate), T, d, E, k, renorm, _ptr(dw_router),
                              _ptr(dbias), _ptr(dx), 1 if dx_accumulate else 0, _ptr(dlogits),
@@ -149,10 +161,7 @@ def moe_permute(x, topk_idx, E, expert_begin=0, num_local=None, cap=None, counts
     row_src = torch.empty(max(cap, 1), dtype=torch.int32, device=dev)
     dst = torch.empty(max(T * k, 1), dtype=torch.int32, device=dev)
     x_perm = torch.empty((max(cap, 1), d), dtype=torch.bfloat16, device=dev)
-    n = ctypes.c_size_t()
-    _check(lib.moe_permute_workspace_bytes(T, E, k, num_local, ctypes.byref(n)),
-           "moe_permute_workspace_bytes")
-    ws = workspace(n.value, dev, "permute")
+    ws = workspace(_ws_bytes("moe_permute_workspace_bytes", T, E, k, num_local), dev, "permute")
     _check(lib.moe_permute(_ptr(x), _ptr(topk_idx), T, d, E, k, expert_begin, num_local,
                            _ptr(offsets), _ptr(cg), _ptr(row_src), _ptr(dst), _ptr(x_perm),
                            _ptr(ws), ws.numel(), _stream()), "moe_permute")
@@ -205,10 +214,7 @@ def moe_grouped_swiglu_fwd(x_perm, expert_offsets, w_gate, w_up, w_down, cap=Non
         h_up = torch.empty((max(cap, 1), f), dtype=torch.bfloat16, device=dev)
     if y_perm is None:
         y_perm = torch.empty((max(cap, 1), d), dtype=torch.bfloat16, device=dev)
-    n = ctypes.c_size_t()
-    _check(lib.moe_grouped_swiglu_workspace_bytes(cap, E_loc, d, f, 0, ctypes.byref(n)),
-           "moe_grouped_swiglu_workspace_bytes")
-    ws = workspace(n.value, dev, "ffn")
+    ws = workspace(_ws_bytes("moe_grouped_swiglu_workspace_bytes", cap, E_loc, d, f, 0), dev, "ffn")
     _check(lib.moe_grouped_swiglu_fwd(_ptr(x_perm), _ptr(expert_offsets), E_loc, cap, d, f,
                                       _ptr(w_gate), _ptr(w_up), _ptr(w_down), _ptr(h_gate),
                                       _ptr(h_up), _ptr(y_perm), _ptr(ws), ws.numel(), _stream()),
@@ -237,10 +243,8 @@ def moe_grouped_swiglu_bwd(dy_perm, x_perm, h_gate, h_up, expert_offsets, w_gate
             dw_up = torch.empty_like(w_up)
         if dw_down is None:
             dw_down = torch.empty_like(w_down)
-    n = ctypes.c_size_t()
-    _check(lib.moe_grouped_swiglu_workspace_bytes(cap, E_loc, d, f, flags, ctypes.byref(n)),
-           "moe_grouped_swiglu_workspace_bytes")
-    ws = workspace(n.value, dev, "ffn")
+    ws = workspace(_ws_bytes("moe_grouped_swiglu_workspace_bytes", cap, E_loc, d, f, flags), dev,
+                   "ffn")
     _check(lib.moe_grouped_swiglu_bwd(_ptr(dy_perm), _ptr(x_perm), _ptr(h_gate), _ptr(h_up),
                                       _ptr(expert_offsets), E_loc, cap, d, f, _ptr(w_gate),
                                       _ptr(w_up), _ptr(w_down), _ptr(dx_perm), _ptr(dw_gate),
@@ -302,10 +306,8 @@ def moe_ffn_fwd_chunked(x, topk_idx, topk_gate, E, w_gate, w_up, w_down, chunk, 
     f = w_gate.shape[2]
     if out is None:
         out = torch.empty((T, d), dtype=torch.bfloat16, device=x.device)
-    n = ctypes.c_size_t()
-    _check(lib.moe_ffn_fwd_chunked_workspace_bytes(chunk, E, k, num_local, d, f, ctypes.byref(n)),
-           "moe_ffn_fwd_chunked_workspace_bytes")
-    ws = workspace(n.value, x.device, "ffn_fwd_chunked")
+    ws = workspace(_ws_bytes("moe_ffn_fwd_chunked_workspace_bytes", chunk, E, k, num_local, d, f),
+                   x.device, "ffn_fwd_chunked")
     s2 = _stream() if stream2 is None else ctypes.c_void_p(stream2.cuda_stream)
     _check(lib.moe_ffn_fwd_chunked(_ptr(x), _ptr(topk_idx), _ptr(topk_gate), T, d, E, k,
                                    expert_begin, num_local, f, _ptr(w_gate), _ptr(w_up),
@@ -330,11 +332,8 @@ def moe_ffn_fwd_row_chunked(x, topk_idx, topk_gate, E, w_gate, w_up, w_down, chu
     f = w_gate.shape[2]
     if out is None:
         out = torch.empty((T, d), dtype=torch.bfloat16, device=x.device)
-    n = ctypes.c_size_t()
-    _check(lib.moe_ffn_fwd_row_chunked_workspace_bytes(T, E, k, num_local, d, f, chunk_rows,
-                                                       ctypes.byref(n)),
-           "moe_ffn_fwd_row_chunked_workspace_bytes")
-    ws = workspace(n.value, x.device, "ffn_fwd_row_chunked")
+    ws = workspace(_ws_bytes("moe_ffn_fwd_row_chunked_workspace_bytes", T, E, k, num_local, d, f,
+                             chunk_rows), x.device, "ffn_fwd_row_chunked")
     s2 = _stream() if stream2 is None else ctypes.c_void_p(stream2.cuda_stream)
     _check(lib.moe_ffn_fwd_row_chunked(_ptr(x), _ptr(topk_idx), _ptr(topk_gate), T, d, E, k,
                                        expert_begin, num_local, f, _ptr(w_gate), _ptr(w_up),
@@ -345,10 +344,8 @@ def moe_ffn_fwd_row_chunked(x, topk_idx, topk_gate, E, w_gate, w_up, w_down, chu
 
 # ------------------------------------------------------- vocabulary loss
 def _vocab_ws(N, H, V, vblock, device):
-    n = ctypes.c_size_t()
-    _check(lib.moe_vocab_loss_workspace_bytes(N, H, V, vblock, ctypes.byref(n)),
-           "moe_vocab_loss_workspace_bytes")
-    return workspace(n.value, device, "vocab_loss")
+    return workspace(_ws_bytes("moe_vocab_loss_workspace_bytes", N, H, V, vblock), device,
+                     "vocab_loss")
 
 
 def moe_vocab_loss_fwd(x, w_voc, target, vblock, loss=None, lse=None):
