@@ -328,7 +328,7 @@ int moe_ffn_fwd_row_chunked(const moe_bf16* x, const int32_t* topk_idx, const fl
  * workspace: moe_vocab_loss_workspace_bytes() bytes (serves both calls;
  * 2 N vblock bytes of logit gradients, up to 8 fp32 N x H slabs of dx
  * partial sums and N vblock / 8 bytes of per-64-column pairs; when V is not
- * a multiple of 8, also padded copies of one block of W and of dW).  It does
+ * a multiple of 8, also a padded copy of one block of W).  It does
  * not depend on V otherwise.  All products run on the library's bf16
  * matrix-core kernel with fp32 accumulation.
  */

@@ -507,7 +507,8 @@ MOE_API int moe_vocab_loss_fwd(const moe_bf16* x, const moe_bf16* w_voc, const i
     OPT(workspace);
   }
   return hip_status(moe::launch_vocab_fwd(x, w_voc, target, N, H, V, vblock, loss, lse,
-                                          workspace, static_cast<hipStream_t>(stream)),
+                                          workspace, workspace_bytes,
+                                          static_cast<hipStream_t>(stream)),
                     fn);
 }
 

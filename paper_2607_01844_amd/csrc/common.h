@@ -121,7 +121,7 @@ size_t vocab_fwd_ws_bytes(int64_t N, int H, int64_t V, int64_t vblock);
 size_t vocab_bwd_ws_bytes(int64_t N, int H, int64_t V, int64_t vblock);
 hipError_t launch_vocab_fwd(const uint16_t* x, const uint16_t* w, const int32_t* target,
                             int64_t N, int H, int64_t V, int64_t vblock, float* loss, float* lse,
-                            void* ws, hipStream_t s);
+                            void* ws, size_t ws_bytes, hipStream_t s);
 hipError_t launch_vocab_bwd(const uint16_t* x, const uint16_t* w, const int32_t* target,
                             const float* lse, const float* dloss, int64_t N, int H, int64_t V,
                             int64_t vblock, uint16_t* dx, uint16_t* dw, void* ws, hipStream_t s);
@@ -189,7 +189,8 @@ hipError_t launch_router_dx_mfma(const uint16_t* dl3, const uint16_t* w3, int64_
 //     zeros for c in [vb, gp);
 //   dx: dxa[b][n][h] (=, first) or (+=) sum over c in batch b's kspan
 //     columns of G[n][c] W[h][bc0 + c];
-//   dw: dw[h][cc0 + c] = bf16(sum_n x[n][h] G[n][c]), row pitch ldd.
+//   dw: dw[h][cc0 + c] = bf16(sum_n x[n][h] G[n][c]), row pitch ldd (rows of
+//     any alignment).
 hipError_t launch_vocab_logits_mfma(const uint16_t* x, const uint16_t* w, int64_t ldw, int64_t bc0,
                                     int64_t v0, int N, int H, int vb, const int32_t* target,
                                     float* part, float* yt, hipStream_t s);

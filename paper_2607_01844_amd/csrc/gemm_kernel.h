@@ -455,6 +455,19 @@ struct GemmArgs {
   int flag;                 // RT_DX: add to dx; VOC_DX: first block (store, no add)
 };
 
+// Eight bf16 to an address of any alignment, the first n where n < 8 (the
+// end of a row of dW whose length is no multiple of 8).
+__device__ __forceinline__ void store_any(uint16_t* to, const uint4& v, int n) {
+  if (n >= 8) {
+    __builtin_memcpy(to, &v, sizeof v);
+  } else {
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int q = 0; q < 7; ++q)
+      if (q < n) to[q] = static_cast<uint16_t>(w[q / 2] >> (16 * (q & 1)));
+  }
+}
+
 __device__ __forceinline__ uint2 pack4(float a, float b, float c, float d) {
   return make_uint2(pack_bf16x2(a, b), pack_bf16x2(c, d));
 }
@@ -1177,7 +1190,8 @@ __global__ __launch_bounds__(Geom<S>::NTHR, 2) void grouped_gemm_kernel(GemmArgs
             else if constexpr (MODE == WGRAD_DOWN) out = g.dwd + e * wdf + (int64_t)(m0 + rt) * d;
             else if constexpr (MODE == VOC_GRAD) out = static_cast<uint16_t*>(g.dc) + (int64_t)(m0 + rt) * g.c_ld;
             else out = static_cast<uint16_t*>(g.dc) + (int64_t)(m0 + rt) * g.c_ld + g.cc0;  // VOC_DW
-            *reinterpret_cast<uint4*>(out + col) = v;
+            if constexpr (MODE == VOC_DW) store_any(out + col, v, g.dN - col);
+            else *reinterpret_cast<uint4*>(out + col) = v;
           }
         });
         fence();
@@ -1346,7 +1360,8 @@ __global__ __launch_bounds__(Geom<S>::NTHR, 2) void grouped_gemm_kernel(GemmArgs
               uint16_t* o;
               if constexpr (MODE == WGRAD_DOWN) o = g.dwd + e * wdf + (int64_t)(m0 + rt) * d;
               else o = static_cast<uint16_t*>(g.dc) + (int64_t)(m0 + rt) * g.c_ld + g.cc0;  // VOC_DW
-              *reinterpret_cast<uint4*>(o + col) = v;
+              if constexpr (DENSE) store_any(o + col, v, g.dN - col);
+              else *reinterpret_cast<uint4*>(o + col) = v;
             }
           });
         }

@@ -5,7 +5,9 @@
 //    whose epilogue reduces each row's logits to a (max, sum exp(y - max))
 //    pair per 64 columns and picks up the target's logit; a one-wave-per-row
 //    kernel merges the block's pairs, in column order, into the row's running
-//    pair (blocks in order, so the result repeats bit for bit);
+//    pair (blocks in order, so the result repeats bit for bit).  The forward
+//    walks as many of the caller's blocks at once as its partial pairs fit
+//    the workspace for (fwd_span below);
 //  * backward, per block: the product is recomputed and its epilogue turns
 //    each logit into the logit gradient G = dl ([v == t] - exp(y - lse)),
 //    rounded to bf16 (the only per-block buffer, N x vblock bf16); then
@@ -13,9 +15,9 @@
 //    accumulate into separate fp32 slabs so the product fills the chip) and
 //    dW[:, block] = X^T G (bf16, each column written once).
 // All products run on the library's grouped GEMM kernel (dense modes).  When
-// V is not a multiple of 8 the rows of W and dW are not 16-byte aligned, so
-// each block of W is first copied into a padded buffer (and dW's block goes
-// through one on the way out).
+// V is not a multiple of 8 the rows of W and dW are not 16-byte aligned: each
+// block of W is first copied into a padded buffer (the product's direct loads
+// to LDS want aligned pieces), dW is stored in place.
 #include "common.h"
 
 #include <algorithm>
@@ -107,26 +109,32 @@ __global__ __launch_bounds__(256) void voc_dx_sum_kernel(const float* __restrict
                                                  pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7]));
 }
 
-// wst[h][c] = c < vb ? w[h][v0 + c] : 0 for c < vbp (padded copy of a block)
+// wst[h][c] = c < vb ? w[h][v0 + c] : 0 for c < vbp (padded copy of a block),
+// eight columns a thread
 __global__ __launch_bounds__(256) void voc_stage_kernel(const uint16_t* __restrict__ w, int64_t V,
                                                         int64_t v0, int vb, int vbp, int H,
                                                         uint16_t* __restrict__ wst) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (i >= static_cast<int64_t>(H) * vbp) return;
-  const int64_t h = i / vbp;
-  const int c = static_cast<int>(i - h * vbp);
-  wst[i] = c < vb ? w[h * V + v0 + c] : uint16_t{0};
+  const int per = vbp / 8;
+  if (i >= static_cast<int64_t>(H) * per) return;
+  const int64_t h = i / per;
+  const int c = static_cast<int>(i - h * per) * 8;
+  const uint16_t* src = w + h * V + v0 + c;
+  uint32_t p[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t lo = c + 2 * q < vb ? src[2 * q] : 0u;
+    const uint32_t hi = c + 2 * q + 1 < vb ? src[2 * q + 1] : 0u;
+    p[q] = lo | (hi << 16);
+  }
+  *reinterpret_cast<uint4*>(wst + i * 8) = make_uint4(p[0], p[1], p[2], p[3]);
 }
 
-// dw[h][v0 + c] = dwst[h][c] for c < vb
-__global__ __launch_bounds__(256) void voc_unstage_kernel(const uint16_t* __restrict__ dwst,
-                                                          int vbp, int vb, int H, int64_t V,
-                                                          int64_t v0, uint16_t* __restrict__ dw) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (i >= static_cast<int64_t>(H) * vb) return;
-  const int64_t h = i / vb;
-  const int c = static_cast<int>(i - h * vb);
-  dw[h * V + v0 + c] = dwst[h * vbp + c];
+hipError_t stage(const uint16_t* w, int64_t V, int64_t v0, int vb, int vbp, int H, uint16_t* wst,
+                 hipStream_t s) {
+  const int64_t n = static_cast<int64_t>(H) * (vbp / 8);
+  voc_stage_kernel<<<static_cast<unsigned>(ceil_div(n, 256)), 256, 0, s>>>(w, V, v0, vb, vbp, H, wst);
+  return hipGetLastError();
 }
 
 __global__ __launch_bounds__(256) void voc_zero_bf16_kernel(uint16_t* __restrict__ p, int64_t n) {
@@ -148,13 +156,40 @@ int64_t dx_kspan(int64_t N, int H, int64_t vblock) {
 
 }  // namespace
 
+namespace {
+size_t fwd_bytes(int64_t N, int H, int64_t V, int64_t span);
+// Columns the forward takes at once: the largest multiple of vblock whose
+// partial pairs (and staged copy of W) fit the workspace that
+// moe_vocab_loss_workspace_bytes() asks for, which the backward's buffers
+// set.  One product of many tiles instead of one per block: fewer launches
+// and partly filled last rounds (N = 1000, H = 520, V = 32003 in blocks of
+// 4096: 8 products and merges become 2; N = 4096, H = 2048, V = 200000: 13
+// become 1).
+int64_t fwd_span(int64_t N, int H, int64_t V, int64_t vblock) {
+  const size_t room = std::max(vocab_fwd_ws_bytes(N, H, V, vblock), vocab_bwd_ws_bytes(N, H, V, vblock));
+  const int64_t most = std::min<int64_t>(ceil_div(V, vblock), ((int64_t{1} << 40) - 1) / (N * vblock));
+  int64_t lo = 1, hi = std::max<int64_t>(1, most);  // the largest m in [lo, hi] that fits
+  while (lo < hi) {
+    const int64_t mid = (lo + hi + 1) / 2;
+    if (fwd_bytes(N, H, V, mid * vblock) <= room) lo = mid; else hi = mid - 1;
+  }
+  return lo * vblock;
+}
+}  // namespace
+
 size_t vocab_fwd_ws_bytes(int64_t N, int H, int64_t V, int64_t vblock) {
-  const int64_t vb = std::min(vblock, V);
+  return fwd_bytes(N, H, V, vblock);
+}
+
+namespace {
+size_t fwd_bytes(int64_t N, int H, int64_t V, int64_t span) {
+  const int64_t vb = std::min(span, V);
   size_t b = align_up(sizeof(float) * 2 * static_cast<size_t>(N) * ceil_div(vb, 64), 256);  // pairs
   b += 3 * align_up(sizeof(float) * static_cast<size_t>(N), 256);  // running max, sum; target logit
   if (staged(V)) b += align_up(sizeof(uint16_t) * static_cast<size_t>(H) * align_up(vb, 8), 256);
   return b + 256;
 }
+}  // namespace
 
 size_t vocab_bwd_ws_bytes(int64_t N, int H, int64_t V, int64_t vblock) {
   const int64_t vb = std::min(vblock, V);
@@ -162,15 +197,17 @@ size_t vocab_bwd_ws_bytes(int64_t N, int H, int64_t V, int64_t vblock) {
   const int64_t slabs = ceil_div(vb, dx_kspan(N, H, vblock));
   size_t b = align_up(sizeof(uint16_t) * static_cast<size_t>(N) * vbp, 256);            // G
   b += align_up(sizeof(float) * static_cast<size_t>(slabs) * N * H, 256);                // dX slabs
-  if (staged(V)) b += 2 * align_up(sizeof(uint16_t) * static_cast<size_t>(H) * vbp, 256);  // W, dW
+  if (staged(V)) b += align_up(sizeof(uint16_t) * static_cast<size_t>(H) * vbp, 256);  // W
   return b + 256;
 }
 
 hipError_t launch_vocab_fwd(const uint16_t* x, const uint16_t* w, const int32_t* target,
                             int64_t N, int H, int64_t V, int64_t vblock, float* loss, float* lse,
-                            void* ws, hipStream_t s) {
+                            void* ws, size_t ws_bytes, hipStream_t s) {
   if (N == 0) return hipSuccess;
-  const int64_t vbmax = std::min(vblock, V);
+  // a caller with room for the forward alone gets its blocks one by one
+  const int64_t span = ws_bytes >= vocab_bwd_ws_bytes(N, H, V, vblock) ? fwd_span(N, H, V, vblock) : vblock;
+  const int64_t vbmax = std::min(span, V);
   char* p = static_cast<char*>(ws);
   float* part = reinterpret_cast<float*>(p);
   p += align_up(sizeof(float) * 2 * static_cast<size_t>(N) * ceil_div(vbmax, 64), 256);
@@ -182,15 +219,13 @@ hipError_t launch_vocab_fwd(const uint16_t* x, const uint16_t* w, const int32_t*
   p += align_up(sizeof(float) * static_cast<size_t>(N), 256);
   uint16_t* wst = staged(V) ? reinterpret_cast<uint16_t*>(p) : nullptr;
   const int n = static_cast<int>(N);
-  for (int64_t b0 = 0; b0 < V; b0 += vblock) {
-    const int vb = static_cast<int>(std::min<int64_t>(vblock, V - b0));
+  for (int64_t b0 = 0; b0 < V; b0 += span) {
+    const int vb = static_cast<int>(std::min<int64_t>(span, V - b0));
     const uint16_t* wb = w;
     int64_t ldw = V, bc0 = b0;
     if (wst != nullptr) {
       const int vbp = static_cast<int>(align_up(vb, 8));
-      voc_stage_kernel<<<static_cast<unsigned>(ceil_div(static_cast<int64_t>(H) * vbp, 256)), 256,
-                         0, s>>>(w, V, b0, vb, vbp, H, wst);
-      if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+      if (hipError_t e = stage(w, V, b0, vb, vbp, H, wst, s); e != hipSuccess) return e;
       wb = wst;
       ldw = vbp;
       bc0 = 0;
@@ -227,31 +262,19 @@ hipError_t launch_vocab_bwd(const uint16_t* x, const uint16_t* w, const int32_t*
   p += align_up(sizeof(uint16_t) * static_cast<size_t>(N) * vbpmax, 256);
   float* dxa = reinterpret_cast<float*>(p);
   p += align_up(sizeof(float) * static_cast<size_t>(slabs) * N * H, 256);
-  uint16_t* wst = nullptr;
-  uint16_t* dwst = nullptr;
-  if (staged(V)) {
-    wst = reinterpret_cast<uint16_t*>(p);
-    p += align_up(sizeof(uint16_t) * static_cast<size_t>(H) * vbpmax, 256);
-    dwst = reinterpret_cast<uint16_t*>(p);
-  }
+  uint16_t* wst = staged(V) ? reinterpret_cast<uint16_t*>(p) : nullptr;
   const int n = static_cast<int>(N);
   for (int64_t b0 = 0; b0 < V; b0 += vblock) {
     const int vb = static_cast<int>(std::min<int64_t>(vblock, V - b0));
     const int64_t gp = align_up(vb, 8);
     const uint16_t* wb = w;
     int64_t ldw = V, bc0 = b0;
-    uint16_t* dwb = dw;
-    int64_t ldd = V, cc0 = b0;
     if (wst != nullptr) {
-      voc_stage_kernel<<<static_cast<unsigned>(ceil_div(static_cast<int64_t>(H) * gp, 256)), 256,
-                         0, s>>>(w, V, b0, vb, static_cast<int>(gp), H, wst);
-      if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+      if (hipError_t e = stage(w, V, b0, vb, static_cast<int>(gp), H, wst, s); e != hipSuccess)
+        return e;
       wb = wst;
       ldw = gp;
       bc0 = 0;
-      dwb = dwst;
-      ldd = gp;
-      cc0 = 0;
     }
     if (hipError_t e = launch_vocab_grad_mfma(x, wb, ldw, bc0, b0, n, H, vb, target, lse, dloss, G,
                                               gp, s);
@@ -260,13 +283,8 @@ hipError_t launch_vocab_bwd(const uint16_t* x, const uint16_t* w, const int32_t*
     if (hipError_t e = launch_vocab_dx_mfma(G, gp, wb, ldw, bc0, n, H, vb, kspan, b0 == 0, dxa, s);
         e != hipSuccess)
       return e;
-    if (hipError_t e = launch_vocab_dw_mfma(x, G, gp, n, H, vb, dwb, ldd, cc0, s); e != hipSuccess)
+    if (hipError_t e = launch_vocab_dw_mfma(x, G, gp, n, H, vb, dw, V, b0, s); e != hipSuccess)
       return e;
-    if (dwst != nullptr) {
-      voc_unstage_kernel<<<static_cast<unsigned>(ceil_div(static_cast<int64_t>(H) * vb, 256)), 256,
-                           0, s>>>(dwst, static_cast<int>(gp), vb, H, V, b0, dw);
-      if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
-    }
   }
   const int64_t nx = N * H;
   voc_dx_sum_kernel<<<static_cast<unsigned>(ceil_div(nx / 8, 256)), 256, 0, s>>>(dxa, slabs, nx, dx);
