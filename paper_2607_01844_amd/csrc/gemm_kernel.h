@@ -468,6 +468,16 @@ __device__ __forceinline__ void store_any(uint16_t* to, const uint4& v, int n) {
   }
 }
 
+// Eight bf16 of y_perm or dx_perm, which no later tile of the launch reads:
+// past the L2's working set, in whole 128-byte pieces.  Plain stores push
+// operand slabs out of the 4 MiB L2s: gate/up data gradient of mid 309 -> 301
+// us, of long 12.6 -> 12.3 ms, and the combine that follows 29.7 -> 25 us at
+// mid.  (The other outputs gain nothing or lose: 64-byte pieces, gate/up
+// weight gradient of mid 389 -> 430 us.)
+__device__ __forceinline__ void store_nt(uint16_t* to, const uint4& v) {
+  __builtin_nontemporal_store(u32x4a{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4a*>(to));
+}
+
 __device__ __forceinline__ uint2 pack4(float a, float b, float c, float d) {
   return make_uint2(pack_bf16x2(a, b), pack_bf16x2(c, d));
 }
@@ -1191,6 +1201,7 @@ __global__ __launch_bounds__(Geom<S>::NTHR, 2) void grouped_gemm_kernel(GemmArgs
             else if constexpr (MODE == VOC_GRAD) out = static_cast<uint16_t*>(g.dc) + (int64_t)(m0 + rt) * g.c_ld;
             else out = static_cast<uint16_t*>(g.dc) + (int64_t)(m0 + rt) * g.c_ld + g.cc0;  // VOC_DW
             if constexpr (MODE == VOC_DW) store_any(out + col, v, g.dN - col);
+            else if constexpr (MODE == FWD_DOWN || MODE == DGRAD_GATE_UP) store_nt(out + col, v);
             else *reinterpret_cast<uint4*>(out + col) = v;
           }
         });
