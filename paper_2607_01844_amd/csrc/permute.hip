@@ -205,8 +205,10 @@ __global__ __launch_bounds__(256) void perm_rank_kernel(const int32_t* __restric
 // (expert id and rank kept in registers), per-wave counts and the experts'
 // offsets are scanned in LDS, then rows are written.  Bound by latency: the
 // three launches it replaces spend theirs on starting and on loads of each
-// other's few results (24576 assignments, 64 experts: 28 -> 12 us).
-constexpr int SMALL_A = 32768;  // above, one workgroup's serial steps outlast three launches
+// other's few results (3300 assignments, 12 experts: 19 -> 7 us; 512: 11 ->
+// 4).  Beyond SMALL_A the ballots of one CU's waves outlast three launches
+// spread over the chip (24576 assignments, 64 experts: 35 us against 28).
+constexpr int SMALL_A = 8192;
 constexpr int SMALL_E = 512;    // 32 KiB of per-wave counts
 constexpr int SMALL_W = 16;     // waves
 template <int R>
@@ -302,6 +304,14 @@ __global__ __launch_bounds__(64 * SMALL_W) void perm_small_kernel(
   }
 }
 
+// One wave per token: 4 KiB of x[t] at a time in registers, written to each
+// of the token's local rows (their numbers in scalar registers; KMAX >= k
+// slots, unrolled).  Lanes past the row's end load its last chunk, so that
+// every load is unconditional: with conditional ones the compiler moved the
+// row to LDS, waited for each load in turn and read the launch packet from
+// host memory to number the threads (T = 1100, d = 520, k = 3: 17 us against
+// 5.5).
+template <int KMAX>
 __global__ __launch_bounds__(256) void perm_gather_kernel(const uint16_t* __restrict__ x,
                                                           const int32_t* __restrict__ dst,
                                                           int64_t T, int d, int k,
@@ -311,27 +321,22 @@ __global__ __launch_bounds__(256) void perm_gather_kernel(const uint16_t* __rest
   if (t >= T) return;
   const int my = (lane < k) ? dst[t * k + lane] : -1;
   if (__ballot(my >= 0) == 0ull) return;
-  int ps[MOE_MAX_K];
+  int ps[KMAX];
 #pragma unroll
-  for (int i = 0; i < MOE_MAX_K; ++i) ps[i] = __shfl(my, i, 64);
+  for (int i = 0; i < KMAX; ++i) ps[i] = __builtin_amdgcn_readlane(my, i);  // -1 past k
   const uint4* src = reinterpret_cast<const uint4*>(x + t * d);
   const int nch = d >> 3;
   for (int c0 = lane; c0 < nch; c0 += 4 * 64) {
     uint4 v[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int c = c0 + u * 64;
-      if (c < nch) v[u] = src[c];
-    }
+    for (int u = 0; u < 4; ++u) v[u] = src[min(c0 + 64 * u, nch - 1)];
 #pragma unroll
-    for (int i = 0; i < MOE_MAX_K; ++i) {
-      if (i >= k) break;
-      if (ps[i] < 0) continue;
-      uint4* out = reinterpret_cast<uint4*>(x_perm + static_cast<int64_t>(ps[i]) * d);
+    for (int i = 0; i < KMAX; ++i) {
+      if (ps[i] >= 0) {
+        uint4* out = reinterpret_cast<uint4*>(x_perm + static_cast<int64_t>(ps[i]) * d);
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int c = c0 + u * 64;
-        if (c < nch) out[c] = v[u];
+        for (int u = 0; u < 4; ++u)
+          if (c0 + 64 * u < nch) out[c0 + 64 * u] = v[u];
       }
     }
   }
@@ -405,9 +410,8 @@ hipError_t launch_permute(const uint16_t* x, const int32_t* idx, int64_t T, int 
       perm_small_kernel<4><<<1, 64 * SMALL_W, sh, s>>>(idx, static_cast<int>(A), E, e_begin, E_loc,
                                                       nbits, offsets, counts_global, row_src, dst);
     else
-      perm_small_kernel<32><<<1, 64 * SMALL_W, sh, s>>>(idx, static_cast<int>(A), E, e_begin,
-                                                       E_loc, nbits, offsets, counts_global,
-                                                       row_src, dst);
+      perm_small_kernel<8><<<1, 64 * SMALL_W, sh, s>>>(idx, static_cast<int>(A), E, e_begin, E_loc,
+                                                      nbits, offsets, counts_global, row_src, dst);
     prof_end(K_PERM_RANK, s);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
     return x_perm == nullptr ? hipSuccess : launch_gather(x, dst, T, d, k, x_perm, s);
@@ -481,9 +485,16 @@ hipError_t launch_permute_noalloc(const uint16_t* x, const int32_t* idx, int64_t
 hipError_t launch_gather(const uint16_t* x, const int32_t* dst, int64_t T, int d, int k,
                          uint16_t* x_perm, hipStream_t s) {
   if (T == 0) return hipSuccess;
+  const unsigned grid = static_cast<unsigned>(ceil_div(T, 4));
   prof_begin(K_PERM_GATHER, s);
-  perm_gather_kernel<<<static_cast<unsigned>(ceil_div(T, 4)), 256, 0, s>>>(x, dst, T, d, k,
-                                                                           x_perm);
+  if (k <= 2)
+    perm_gather_kernel<2><<<grid, 256, 0, s>>>(x, dst, T, d, k, x_perm);
+  else if (k <= 4)
+    perm_gather_kernel<4><<<grid, 256, 0, s>>>(x, dst, T, d, k, x_perm);
+  else if (k <= 8)
+    perm_gather_kernel<8><<<grid, 256, 0, s>>>(x, dst, T, d, k, x_perm);
+  else
+    perm_gather_kernel<16><<<grid, 256, 0, s>>>(x, dst, T, d, k, x_perm);
   prof_end(K_PERM_GATHER, s);
   return hipGetLastError();
 }
