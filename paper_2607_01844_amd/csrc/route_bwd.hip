@@ -199,33 +199,69 @@ __device__ __forceinline__ void split_bf16(float v, uint16_t& hi, uint16_t& lo) 
 // [3E, ld3): one product over the 3E columns against [hi; lo; hi] of W_r^T
 // sums the three cross terms, and the dW_r product reads the first hi group
 // and the lo group.
+// One wave per token, four experts a lane (8-byte stores where E is a
+// multiple of 4).
 __global__ __launch_bounds__(256) void route_split_dl_kernel(const float* __restrict__ dl,
                                                              int64_t T, int E, int ld3,
                                                              uint16_t* __restrict__ dl3) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (i >= T * ld3) return;
-  const int64_t t = i / ld3;
-  const int c = static_cast<int>(i - t * ld3);
-  uint16_t out = 0;
-  if (c < 3 * E) {
-    const int grp = c / E, e = c - grp * E;
-    uint16_t hi, lo;
-    split_bf16(dl[t * E + e], hi, lo);
-    out = grp == 2 ? lo : hi;
+  const int lane = threadIdx.x & 63;
+  const int64_t t = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
+  if (t >= T) return;
+  const float* src = dl + t * E;
+  uint16_t* out = dl3 + t * ld3;
+  for (int e = 4 * lane; e < E; e += 256) {
+    uint16_t hi[4], lo[4];
+    if ((E & 3) == 0) {
+      const float4 v = *reinterpret_cast<const float4*>(src + e);
+      split_bf16(v.x, hi[0], lo[0]);
+      split_bf16(v.y, hi[1], lo[1]);
+      split_bf16(v.z, hi[2], lo[2]);
+      split_bf16(v.w, hi[3], lo[3]);
+      const uint2 h = make_uint2(hi[0] | (hi[1] << 16), hi[2] | (hi[3] << 16));
+      *reinterpret_cast<uint2*>(out + e) = h;
+      *reinterpret_cast<uint2*>(out + E + e) = h;
+      *reinterpret_cast<uint2*>(out + 2 * E + e) = make_uint2(lo[0] | (lo[1] << 16), lo[2] | (lo[3] << 16));
+    } else {
+      for (int q = 0; q < 4 && e + q < E; ++q) {
+        split_bf16(src[e + q], hi[0], lo[0]);
+        out[e + q] = hi[0];
+        out[E + e + q] = hi[0];
+        out[2 * E + e + q] = lo[0];
+      }
+    }
   }
-  dl3[i] = out;
+  if (lane < ld3 - 3 * E) out[3 * E + lane] = 0;
 }
-// W_r [d][E] -> w3 [3E][d] = [hi; lo; hi] of W_r^T
+// W_r [d][E] -> w3 [3E][d] = [hi; lo; hi] of W_r^T: 64 hidden rows x 32
+// experts a block, transposed through LDS so that both sides are contiguous
+// (element by element d = 7168, E = 384 took 45 us).
+constexpr int SW_J = 64, SW_E = 32;
 __global__ __launch_bounds__(256) void route_split_w_kernel(const float* __restrict__ w, int d,
                                                             int E, uint16_t* __restrict__ w3) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (i >= static_cast<int64_t>(3) * E * d) return;
-  const int64_t r = i / d;
-  const int j = static_cast<int>(i - r * d);
-  const int grp = static_cast<int>(r / E), e = static_cast<int>(r - static_cast<int64_t>(grp) * E);
-  uint16_t hi, lo;
-  split_bf16(w[static_cast<int64_t>(j) * E + e], hi, lo);
-  w3[i] = grp == 1 ? lo : hi;
+  __shared__ float tile[SW_J][SW_E + 1];
+  const int j0 = blockIdx.x * SW_J, e0 = blockIdx.y * SW_E;
+#pragma unroll
+  for (int i = 0; i < SW_J * SW_E / 256; ++i) {
+    const int q = threadIdx.x + 256 * i, j = q / SW_E, e = q % SW_E;
+    tile[j][e] = j0 + j < d && e0 + e < E ? w[static_cast<int64_t>(j0 + j) * E + e0 + e] : 0.0f;
+  }
+  __syncthreads();
+  const int e = threadIdx.x >> 3, j = (threadIdx.x & 7) * 8;  // eight hidden rows of one expert
+  if (e0 + e >= E || j0 + j >= d) return;  // d is a multiple of 8
+  uint32_t h[4], l[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    uint16_t ha, la, hb, lb;
+    split_bf16(tile[j + 2 * q][e], ha, la);
+    split_bf16(tile[j + 2 * q + 1][e], hb, lb);
+    h[q] = ha | (static_cast<uint32_t>(hb) << 16);
+    l[q] = la | (static_cast<uint32_t>(lb) << 16);
+  }
+  uint16_t* out = w3 + static_cast<int64_t>(e0 + e) * d + j0 + j;
+  const int64_t grp = static_cast<int64_t>(E) * d;
+  *reinterpret_cast<uint4*>(out) = make_uint4(h[0], h[1], h[2], h[3]);
+  *reinterpret_cast<uint4*>(out + grp) = make_uint4(l[0], l[1], l[2], l[3]);
+  *reinterpret_cast<uint4*>(out + 2 * grp) = make_uint4(h[0], h[1], h[2], h[3]);
 }
 // bpart[c][e] = sum over the tokens of chunk c of dl[t][e].  Lane = expert
 // (64 per block); wave w of the block's 16 sums the chunk's tokens t0 + w,
@@ -395,8 +431,7 @@ hipError_t launch_route_bwd_mfma(const uint16_t* x, const float* w, int64_t T, i
   uint16_t* w3 = reinterpret_cast<uint16_t*>(p);
 
   prof_begin(K_ROUTE_SPLIT, s);
-  route_split_dl_kernel<<<static_cast<unsigned>(ceil_div(T * ld3, 256)), 256, 0, s>>>(dl, T, E,
-                                                                                    ld3, dl3);
+  route_split_dl_kernel<<<static_cast<unsigned>(ceil_div(T, 4)), 256, 0, s>>>(dl, T, E, ld3, dl3);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   if (dbias != nullptr) {
     route_dbias_part_kernel<<<dim3(static_cast<unsigned>(ceil_div(E, 64)),
@@ -418,7 +453,9 @@ hipError_t launch_route_bwd_mfma(const uint16_t* x, const float* w, int64_t T, i
   }
   if (dx == nullptr) return hipSuccess;
   prof_begin(K_ROUTE_SPLIT, s);
-  route_split_w_kernel<<<static_cast<unsigned>(ceil_div(3 * nw, 256)), 256, 0, s>>>(w, d, E, w3);
+  route_split_w_kernel<<<dim3(static_cast<unsigned>(ceil_div(d, SW_J)),
+                              static_cast<unsigned>(ceil_div(E, SW_E))),
+                         256, 0, s>>>(w, d, E, w3);
   prof_end(K_ROUTE_SPLIT, s);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   // dx [+]= dl3 w3 over the 3E columns, rounded to bf16 once
