@@ -309,8 +309,9 @@ __global__ __launch_bounds__(64 * SMALL_W) void perm_small_kernel(
 // slots, unrolled).  Lanes past the row's end load its last chunk, so that
 // every load is unconditional: with conditional ones the compiler moved the
 // row to LDS, waited for each load in turn and read the launch packet from
-// host memory to number the threads (T = 1100, d = 520, k = 3: 17 us against
-// 5.5).
+// host memory to number the threads (T = 1100, d = 520, k = 3: 18.5 us against
+// 6.7).  The loaded row is opaque to it: left alone, it loads the row again
+// for every slot (T = 65536, d = 4096, k = 8: 1295 us against 960).
 template <int KMAX>
 __global__ __launch_bounds__(256) void perm_gather_kernel(const uint16_t* __restrict__ x,
                                                           const int32_t* __restrict__ dst,
@@ -330,6 +331,9 @@ __global__ __launch_bounds__(256) void perm_gather_kernel(const uint16_t* __rest
     uint4 v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) v[u] = src[min(c0 + 64 * u, nch - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      asm volatile("" : "+v"(v[u].x), "+v"(v[u].y), "+v"(v[u].z), "+v"(v[u].w));
 #pragma unroll
     for (int i = 0; i < KMAX; ++i) {
       if (ps[i] >= 0) {
