@@ -329,8 +329,11 @@ int moe_ffn_fwd_row_chunked(const moe_bf16* x, const int32_t* topk_idx, const fl
  * 2 N vblock bytes of logit gradients, up to 8 fp32 N x H slabs of dx
  * partial sums and N vblock / 8 bytes of per-64-column pairs; when V is not
  * a multiple of 8, also a padded copy of one block of W).  It does
- * not depend on V otherwise.  All products run on the library's bf16
- * matrix-core kernel with fp32 accumulation.
+ * not depend on V otherwise, except that rows too long for the products'
+ * addressing (256 rows of V bf16 values beyond 2^31 bytes: V above about 4
+ * million) go through the same copy, and blocks that long are cut.  All
+ * products run on the library's bf16 matrix-core kernel with fp32
+ * accumulation.
  */
 int moe_vocab_loss_workspace_bytes(int64_t N, int H, int64_t V, int64_t vblock, size_t* bytes);
 int moe_vocab_loss_fwd(const moe_bf16* x, const moe_bf16* w_voc, const int32_t* target, int64_t N,

@@ -17,7 +17,10 @@
 // All products run on the library's grouped GEMM kernel (dense modes).  When
 // V is not a multiple of 8 the rows of W and dW are not 16-byte aligned: each
 // block of W is first copied into a padded buffer (the product's direct loads
-// to LDS want aligned pieces), dW is stored in place.
+// to LDS want aligned pieces), dW is stored in place.  The same copy takes the
+// place of rows so long that a tile's rows lie further apart than a buffer
+// descriptor reaches (beyond 34 million columns in the forward, 4 million in
+// the backward), and blocks longer than that are cut (reach, below).
 #include "common.h"
 
 #include <algorithm>
@@ -142,7 +145,36 @@ __global__ __launch_bounds__(256) void voc_zero_bf16_kernel(uint16_t* __restrict
   if (i < n) p[i] = 0;
 }
 
-bool staged(int64_t V) { return (V % 8) != 0; }
+// The products address a tile's rows of an operand by 32-bit offsets from the
+// first, within the 2^31 - 16 bytes of a buffer descriptor: true if `rows`
+// rows of `pitch` elements, the last read up to element `tail`, fit.  Rows per
+// operand: 32 (one half step) where the contraction index runs over rows (W in
+// the logits, G in dW), 256 (a tile) where it runs along them (G and W in dX).
+constexpr int64_t REACH = 0x7ffffff0;
+bool reach(int64_t rows, int64_t pitch, int64_t tail) {
+  return 2 * ((rows - 1) * pitch + tail) <= REACH;
+}
+// the longest pitch (a multiple of 64) whose `rows` rows fit
+int64_t max_pitch(int64_t rows) { return REACH / (2 * rows) / 64 * 64; }
+
+// W read through a padded copy of a block?
+bool staged_fwd(int H, int64_t V) {
+  return (V % 8) != 0 || !reach(std::min(H, 32), V, 128);
+}
+bool staged_bwd(int H, int64_t V, int64_t vb) {
+  return staged_fwd(H, V) || !reach(std::min(H, 256), V, std::min(vb, V));
+}
+// The caller's block, cut where the copy (forward) or G and the copy
+// (backward) would have rows out of reach.
+int64_t fwd_block(int H, int64_t V, int64_t vblock) {
+  const int64_t most = max_pitch(std::min(H, 32));
+  return staged_fwd(H, V) && std::min(vblock, V) > most ? most : vblock;
+}
+int64_t bwd_block(int64_t N, int H, int64_t V, int64_t vblock) {
+  const int64_t rows = std::max<int64_t>(N, staged_bwd(H, V, vblock) ? H : 1);
+  const int64_t most = max_pitch(std::min<int64_t>(rows, 256));
+  return std::min(vblock, V) > most ? most : vblock;
+}
 
 // K ranges of the dX product: enough (row tile x column tile x range) work
 // items for about two per compute unit of a 256-CU device, each range at
@@ -164,10 +196,14 @@ size_t fwd_bytes(int64_t N, int H, int64_t V, int64_t span);
 // set.  One product of many tiles instead of one per block: fewer launches
 // and partly filled last rounds (N = 1000, H = 520, V = 32003 in blocks of
 // 4096: 8 products and merges become 2; N = 4096, H = 2048, V = 200000: 13
-// become 1).
+// become 1).  A copy of W stays within reach and one launch (2^31 threads of
+// eight columns).
 int64_t fwd_span(int64_t N, int H, int64_t V, int64_t vblock) {
   const size_t room = std::max(vocab_fwd_ws_bytes(N, H, V, vblock), vocab_bwd_ws_bytes(N, H, V, vblock));
-  const int64_t most = std::min<int64_t>(ceil_div(V, vblock), ((int64_t{1} << 40) - 1) / (N * vblock));
+  vblock = fwd_block(H, V, vblock);
+  int64_t most = std::min<int64_t>(ceil_div(V, vblock), ((int64_t{1} << 40) - 1) / (N * vblock));
+  if (staged_fwd(H, V))
+    most = std::min(most, std::min(max_pitch(std::min(H, 32)), (int64_t{1} << 34) / H) / vblock);
   int64_t lo = 1, hi = std::max<int64_t>(1, most);  // the largest m in [lo, hi] that fits
   while (lo < hi) {
     const int64_t mid = (lo + hi + 1) / 2;
@@ -178,7 +214,7 @@ int64_t fwd_span(int64_t N, int H, int64_t V, int64_t vblock) {
 }  // namespace
 
 size_t vocab_fwd_ws_bytes(int64_t N, int H, int64_t V, int64_t vblock) {
-  return fwd_bytes(N, H, V, vblock);
+  return fwd_bytes(N, H, V, fwd_block(H, V, vblock));
 }
 
 namespace {
@@ -186,18 +222,21 @@ size_t fwd_bytes(int64_t N, int H, int64_t V, int64_t span) {
   const int64_t vb = std::min(span, V);
   size_t b = align_up(sizeof(float) * 2 * static_cast<size_t>(N) * ceil_div(vb, 64), 256);  // pairs
   b += 3 * align_up(sizeof(float) * static_cast<size_t>(N), 256);  // running max, sum; target logit
-  if (staged(V)) b += align_up(sizeof(uint16_t) * static_cast<size_t>(H) * align_up(vb, 8), 256);
+  if (staged_fwd(H, V))
+    b += align_up(sizeof(uint16_t) * static_cast<size_t>(H) * align_up(vb, 8), 256);
   return b + 256;
 }
 }  // namespace
 
 size_t vocab_bwd_ws_bytes(int64_t N, int H, int64_t V, int64_t vblock) {
+  vblock = bwd_block(N, H, V, vblock);
   const int64_t vb = std::min(vblock, V);
   const int64_t vbp = align_up(vb, 8);
   const int64_t slabs = ceil_div(vb, dx_kspan(N, H, vblock));
   size_t b = align_up(sizeof(uint16_t) * static_cast<size_t>(N) * vbp, 256);            // G
   b += align_up(sizeof(float) * static_cast<size_t>(slabs) * N * H, 256);                // dX slabs
-  if (staged(V)) b += align_up(sizeof(uint16_t) * static_cast<size_t>(H) * vbp, 256);  // W
+  if (staged_bwd(H, V, vblock))
+    b += align_up(sizeof(uint16_t) * static_cast<size_t>(H) * vbp, 256);  // W
   return b + 256;
 }
 
@@ -206,7 +245,8 @@ hipError_t launch_vocab_fwd(const uint16_t* x, const uint16_t* w, const int32_t*
                             void* ws, size_t ws_bytes, hipStream_t s) {
   if (N == 0) return hipSuccess;
   // a caller with room for the forward alone gets its blocks one by one
-  const int64_t span = ws_bytes >= vocab_bwd_ws_bytes(N, H, V, vblock) ? fwd_span(N, H, V, vblock) : vblock;
+  const int64_t span = ws_bytes >= vocab_bwd_ws_bytes(N, H, V, vblock) ? fwd_span(N, H, V, vblock)
+                                                                         : fwd_block(H, V, vblock);
   const int64_t vbmax = std::min(span, V);
   char* p = static_cast<char*>(ws);
   float* part = reinterpret_cast<float*>(p);
@@ -217,7 +257,7 @@ hipError_t launch_vocab_fwd(const uint16_t* x, const uint16_t* w, const int32_t*
   p += align_up(sizeof(float) * static_cast<size_t>(N), 256);
   float* yt = reinterpret_cast<float*>(p);
   p += align_up(sizeof(float) * static_cast<size_t>(N), 256);
-  uint16_t* wst = staged(V) ? reinterpret_cast<uint16_t*>(p) : nullptr;
+  uint16_t* wst = staged_fwd(H, V) ? reinterpret_cast<uint16_t*>(p) : nullptr;
   const int n = static_cast<int>(N);
   for (int64_t b0 = 0; b0 < V; b0 += span) {
     const int vb = static_cast<int>(std::min<int64_t>(span, V - b0));
@@ -253,6 +293,7 @@ hipError_t launch_vocab_bwd(const uint16_t* x, const uint16_t* w, const int32_t*
     voc_zero_bf16_kernel<<<static_cast<unsigned>(ceil_div(nw, 256)), 256, 0, s>>>(dw, nw);
     return hipGetLastError();
   }
+  vblock = bwd_block(N, H, V, vblock);
   const int64_t vbmax = std::min(vblock, V);
   const int64_t vbpmax = align_up(vbmax, 8);
   const int kspan = static_cast<int>(dx_kspan(N, H, vblock));
@@ -262,7 +303,7 @@ hipError_t launch_vocab_bwd(const uint16_t* x, const uint16_t* w, const int32_t*
   p += align_up(sizeof(uint16_t) * static_cast<size_t>(N) * vbpmax, 256);
   float* dxa = reinterpret_cast<float*>(p);
   p += align_up(sizeof(float) * static_cast<size_t>(slabs) * N * H, 256);
-  uint16_t* wst = staged(V) ? reinterpret_cast<uint16_t*>(p) : nullptr;
+  uint16_t* wst = staged_bwd(H, V, vblock) ? reinterpret_cast<uint16_t*>(p) : nullptr;
   const int n = static_cast<int>(N);
   for (int64_t b0 = 0; b0 < V; b0 += vblock) {
     const int vb = static_cast<int>(std::min<int64_t>(vblock, V - b0));

@@ -156,3 +156,29 @@ def test_row_chunked_workspace_layout(lib):
     assert n4.value < 0.65 * full
     assert n8.value < 0.45 * full
     assert abs((n4.value - fixed) / (n8.value - fixed) - 2) < 0.05
+
+
+def test_vocab_workspace_of_long_rows():
+    """W goes through a copy of one block where V is not a multiple of 8 or a
+    tile's rows of V values span more than 2^31 bytes, and no block is longer
+    than those rows allow; ordinary sizes have no copy."""
+    from paper_2607_01844_amd import moe
+
+    def query(N, H, V, vb):
+        n = ctypes.c_size_t()
+        assert moe.lib.moe_vocab_loss_workspace_bytes(N, H, V, vb, ctypes.byref(n)) == 0
+        return n.value
+
+    N, H, vb = 4096, 2048, 16384
+    copy = 2 * H * vb
+    base = query(N, H, 200000, vb)
+    assert query(N, H, 4_000_000, vb) == base
+    assert query(N, H, 200001, vb) == query(N, H, 9_000_000, vb) == base + copy
+    # blocks are cut: the backward's where 256 rows of gradients would span more
+    assert query(N, 8, 1 << 30, 1 << 23) == query(N, 8, 1 << 30, 1 << 24) < \
+        2 * (N + 8) * (1 << 22) + (1 << 24)
+    # and the forward's where 32 rows of the copy would
+    assert query(N, H, 1 << 30, 1 << 26) == query(N, H, 1 << 30, 1 << 27) < \
+        (H + N // 8) * (1 << 26)
+    # few rows on both sides: a block may be that long
+    assert query(8, 8, 1 << 24, 1 << 24) >= 2 * 8 * (1 << 24)
