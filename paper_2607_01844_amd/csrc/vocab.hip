@@ -296,7 +296,9 @@ hipError_t launch_vocab_bwd(const uint16_t* x, const uint16_t* w, const int32_t*
   vblock = bwd_block(N, H, V, vblock);
   const int64_t vbmax = std::min(vblock, V);
   const int64_t vbpmax = align_up(vbmax, 8);
-  const int kspan = static_cast<int>(dx_kspan(N, H, vblock));
+  // a range longer than the block is the block (vblock itself may exceed an int)
+  const int kspan = static_cast<int>(
+      std::min<int64_t>(dx_kspan(N, H, vblock), static_cast<int64_t>(align_up(vbmax, 64))));
   const int slabs = static_cast<int>(ceil_div(vbmax, kspan));  // the first block fills them all
   char* p = static_cast<char*>(ws);
   uint16_t* G = reinterpret_cast<uint16_t*>(p);

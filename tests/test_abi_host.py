@@ -4,6 +4,8 @@ invalid arguments on the host before any HIP call."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -156,6 +158,18 @@ def test_row_chunked_workspace_layout(lib):
     assert n4.value < 0.65 * full
     assert n8.value < 0.45 * full
     assert abs((n4.value - fixed) / (n8.value - fixed) - 2) < 0.05
+
+
+@pytest.mark.skipif(not _no_gpu(), reason="dummy pointers are only safe without a GPU")
+@pytest.mark.parametrize("vblock", [1 << 31, 1 << 34, 1 << 35, (1 << 40) - 8])
+def test_vocab_block_beyond_an_int_reaches_the_launch(vblock):
+    """vblock may exceed V by any factor (N vblock < 2^40); the host's plan
+    then comes to the first launch, which fails for want of a device.  In a
+    process of its own: a wrong plan divided by zero."""
+    code = ("import ctypes\nfrom paper_2607_01844_amd import moe\nP = ctypes.c_void_p(4096)\n"
+            f"print(moe.lib.moe_vocab_loss_bwd(P, P, P, P, P, 1, 8, 9, {vblock}, P, P, P, 1 << 30, None))")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.strip() == "-4", (r.returncode, r.stdout, r.stderr)
 
 
 def test_vocab_workspace_of_long_rows():
