@@ -333,7 +333,8 @@ int moe_ffn_fwd_row_chunked(const moe_bf16* x, const int32_t* topk_idx, const fl
  * addressing (256 rows of V bf16 values beyond 2^31 bytes: V above about 4
  * million) go through the same copy, and blocks that long are cut.  All
  * products run on the library's bf16 matrix-core kernel with fp32
- * accumulation.
+ * accumulation.  The results are a function of the inputs and vblock, bit
+ * for bit; a larger workspace does not change them.
  */
 int moe_vocab_loss_workspace_bytes(int64_t N, int H, int64_t V, int64_t vblock, size_t* bytes);
 int moe_vocab_loss_fwd(const moe_bf16* x, const moe_bf16* w_voc, const int32_t* target, int64_t N,

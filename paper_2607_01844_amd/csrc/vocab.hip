@@ -5,9 +5,10 @@
 //    whose epilogue reduces each row's logits to a (max, sum exp(y - max))
 //    pair per 64 columns and picks up the target's logit; a one-wave-per-row
 //    kernel merges the block's pairs, in column order, into the row's running
-//    pair (blocks in order, so the result repeats bit for bit).  The forward
-//    walks as many of the caller's blocks at once as its partial pairs fit
-//    the workspace for (fwd_span below);
+//    pair (blocks in order, so the result is a function of the inputs and
+//    vblock alone, bit for bit).  The forward walks as many of the caller's
+//    blocks at once as its partial pairs fit the workspace for (fwd_span
+//    below);
 //  * backward, per block: the product is recomputed and its epilogue turns
 //    each logit into the logit gradient G = dl ([v == t] - exp(y - lse)),
 //    rounded to bf16 (the only per-block buffer, N x vblock bf16); then
@@ -29,51 +30,72 @@ namespace moe {
 namespace {
 
 // Merge of two (max, sum of exp(y - max)) pairs; an empty pair is (-inf, 0).
+// The fused add is written out, so that every caller rounds alike.
 __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2) {
   const float mm = fmaxf(m, m2);
   if (mm == -__builtin_huge_valf()) return;  // both empty
-  s = s * __expf(m - mm) + s2 * __expf(m2 - mm);
+  s = __builtin_fmaf(s2, __expf(m2 - mm), s * __expf(m - mm));
   m = mm;
 }
 
-// One wave per row n: the block's ng partial pairs part[n][0..ng) merged in
-// order (lane l takes groups l, l + 64, ... ascending, then a fixed xor
-// tree over the lanes), then merged into the row's running pair (m, s).
+// One wave per row n: the partial pairs part[n][0..ng) of the caller's blocks
+// of per groups each (the last may have fewer).  A block's pairs are merged in
+// order (lane l takes groups l, l + 64, ... ascending, then a fixed xor tree
+// over the lanes), then its pair into the row's running pair (m, s), block by
+// block: the result does not depend on how many blocks a launch takes.  Four
+// blocks are reduced at a time, so that their chains of dependent shuffles and
+// exponentials overlap.
 __global__ __launch_bounds__(256) void voc_merge_kernel(const float2* __restrict__ part, int ng,
-                                                        int64_t N, float* __restrict__ m,
+                                                        int per, int64_t N, float* __restrict__ m,
                                                         float* __restrict__ s, int first) {
   const int64_t n = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   if (n >= N) return;
   const float2* row = part + n * ng;
-  float tm = -__builtin_huge_valf(), ts = 0.0f;
-  for (int c = lane; c < ng; c += 64) {
-    const float2 p = row[c];
-    lse_merge(tm, ts, p.x, p.y);
+  float rm = 0.0f, rs = 0.0f;
+  if (!first) {
+    rm = m[n];
+    rs = s[n];
   }
+  constexpr int U = 4;
+  for (int g0 = 0; g0 < ng; g0 += U * per) {
+    float tm[U], ts[U];
 #pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const float m2 = __shfl_xor(tm, o, 64), s2 = __shfl_xor(ts, o, 64);
-    // both lanes of a pair compute the same merge in the same operand order
-    if (lane & o) {
-      float a = m2, b = s2;
-      lse_merge(a, b, tm, ts);
-      tm = a;
-      ts = b;
-    } else {
-      lse_merge(tm, ts, m2, s2);
+    for (int u = 0; u < U; ++u) {
+      tm[u] = -__builtin_huge_valf();
+      ts[u] = 0.0f;
+      const int b = g0 + u * per, e = b + per < ng ? b + per : ng;
+      for (int c = b + lane; c < e; c += 64) {
+        const float2 p = row[c];
+        lse_merge(tm[u], ts[u], p.x, p.y);
+      }
+    }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const float m2 = __shfl_xor(tm[u], o, 64), s2 = __shfl_xor(ts[u], o, 64);
+        // both lanes of a pair compute the same merge in the same operand order
+        float a = lane & o ? m2 : tm[u], b = lane & o ? s2 : ts[u];
+        lse_merge(a, b, lane & o ? tm[u] : m2, lane & o ? ts[u] : s2);
+        tm[u] = a;
+        ts[u] = b;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (g0 + u * per >= ng) break;
+      if (first && g0 == 0 && u == 0) {
+        rm = tm[u];
+        rs = ts[u];
+      } else {
+        lse_merge(rm, rs, tm[u], ts[u]);
+      }
     }
   }
   if (lane == 0) {
-    if (first) {
-      m[n] = tm;
-      s[n] = ts;
-    } else {
-      float rm = m[n], rs = s[n];
-      lse_merge(rm, rs, tm, ts);
-      m[n] = rm;
-      s[n] = rs;
-    }
+    m[n] = rm;
+    s[n] = rs;
   }
 }
 
@@ -196,11 +218,14 @@ size_t fwd_bytes(int64_t N, int H, int64_t V, int64_t span);
 // set.  One product of many tiles instead of one per block: fewer launches
 // and partly filled last rounds (N = 1000, H = 520, V = 32003 in blocks of
 // 4096: 8 products and merges become 2; N = 4096, H = 2048, V = 200000: 13
-// become 1).  A copy of W stays within reach and one launch (2^31 threads of
+// become 1).  Blocks that do not end on a group of 64 columns stay alone: in a
+// longer product their columns would fall into other groups, and the pairs be
+// other sums.  A copy of W stays within reach and one launch (2^31 threads of
 // eight columns).
 int64_t fwd_span(int64_t N, int H, int64_t V, int64_t vblock) {
   const size_t room = std::max(vocab_fwd_ws_bytes(N, H, V, vblock), vocab_bwd_ws_bytes(N, H, V, vblock));
   vblock = fwd_block(H, V, vblock);
+  if (vblock % 64 != 0) return vblock;
   int64_t most = std::min<int64_t>(ceil_div(V, vblock), ((int64_t{1} << 40) - 1) / (N * vblock));
   if (staged_fwd(H, V))
     most = std::min(most, std::min(max_pitch(std::min(H, 32)), (int64_t{1} << 34) / H) / vblock);
@@ -248,6 +273,8 @@ hipError_t launch_vocab_fwd(const uint16_t* x, const uint16_t* w, const int32_t*
   const int64_t span = ws_bytes >= vocab_bwd_ws_bytes(N, H, V, vblock) ? fwd_span(N, H, V, vblock)
                                                                          : fwd_block(H, V, vblock);
   const int64_t vbmax = std::min(span, V);
+  // groups of 64 columns per block of the caller's
+  const int per = static_cast<int>(ceil_div(std::min(fwd_block(H, V, vblock), V), 64));
   char* p = static_cast<char*>(ws);
   float* part = reinterpret_cast<float*>(p);
   p += align_up(sizeof(float) * 2 * static_cast<size_t>(N) * ceil_div(vbmax, 64), 256);
@@ -275,7 +302,7 @@ hipError_t launch_vocab_fwd(const uint16_t* x, const uint16_t* w, const int32_t*
       return e;
     prof_begin(K_VOC_LSE, s);
     voc_merge_kernel<<<static_cast<unsigned>(ceil_div(N, 4)), 256, 0, s>>>(
-        reinterpret_cast<const float2*>(part), static_cast<int>(ceil_div(vb, 64)), N, m, sm,
+        reinterpret_cast<const float2*>(part), static_cast<int>(ceil_div(vb, 64)), per, N, m, sm,
         b0 == 0);
     prof_end(K_VOC_LSE, s);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
