@@ -38,33 +38,37 @@ __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2
   m = mm;
 }
 
-// One wave per row n: the partial pairs part[n][0..ng) of the caller's blocks
-// of per groups each (the last may have fewer).  A block's pairs are merged in
-// order (lane l takes groups l, l + 64, ... ascending, then a fixed xor tree
-// over the lanes), then its pair into the row's running pair (m, s), block by
-// block: the result does not depend on how many blocks a launch takes.  Four
-// blocks are reduced at a time, so that their chains of dependent shuffles and
-// exponentials overlap.
+// W waves per row n: the partial pairs part[n][0..ng) of the caller's blocks
+// of per groups each (the last may have fewer).  One wave merges a block's
+// pairs in order (lane l takes groups l, l + 64, ... ascending, then a fixed
+// xor tree over the lanes); the blocks' pairs then go into the row's running
+// pair (m, s) in order, so the result does not depend on how many blocks a
+// launch takes.  Bound by latency (loads, then twelve dependent shuffles and
+// exponentials a block): with several blocks four waves share a row, two
+// blocks each at a time (N = 1000, H = 520, V = 32003 in blocks of 4096, loss
+// and gradients: 497 us against 503 with one wave a row).
+template <int W>
 __global__ __launch_bounds__(256) void voc_merge_kernel(const float2* __restrict__ part, int ng,
                                                         int per, int64_t N, float* __restrict__ m,
                                                         float* __restrict__ s, int first) {
-  const int64_t n = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (n >= N) return;
+  constexpr int U = W == 1 ? 1 : 2;
+  __shared__ float2 blk[W == 1 ? 1 : U * W];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wv = wave % W;
+  const int64_t n = static_cast<int64_t>(blockIdx.x) * (4 / W) + wave / W;
+  if (n >= N) return;  // W = 4: the whole workgroup
   const float2* row = part + n * ng;
   float rm = 0.0f, rs = 0.0f;
   if (!first) {
     rm = m[n];
     rs = s[n];
   }
-  constexpr int U = 4;
-  for (int g0 = 0; g0 < ng; g0 += U * per) {
+  for (int g0 = 0; g0 < ng; g0 += U * W * per) {
     float tm[U], ts[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       tm[u] = -__builtin_huge_valf();
       ts[u] = 0.0f;
-      const int b = g0 + u * per, e = b + per < ng ? b + per : ng;
+      const int b = g0 + (u * W + wv) * per, e = b + per < ng ? b + per : ng;
       for (int c = b + lane; c < e; c += 64) {
         const float2 p = row[c];
         lse_merge(tm[u], ts[u], p.x, p.y);
@@ -82,18 +86,29 @@ __global__ __launch_bounds__(256) void voc_merge_kernel(const float2* __restrict
         ts[u] = b;
       }
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (g0 + u * per >= ng) break;
-      if (first && g0 == 0 && u == 0) {
-        rm = tm[u];
-        rs = ts[u];
+    if constexpr (W == 1) {
+      if (first && g0 == 0) {
+        rm = tm[0];
+        rs = ts[0];
       } else {
-        lse_merge(rm, rs, tm[u], ts[u]);
+        lse_merge(rm, rs, tm[0], ts[0]);
       }
+    } else {
+      if (lane < U) blk[lane * W + wv] = lane == 0 ? make_float2(tm[0], ts[0]) : make_float2(tm[1], ts[1]);
+      __syncthreads();
+      for (int q = 0; q < U * W && g0 + q * per < ng; ++q) {
+        const float2 p = blk[q];
+        if (first && g0 == 0 && q == 0) {
+          rm = p.x;
+          rs = p.y;
+        } else {
+          lse_merge(rm, rs, p.x, p.y);
+        }
+      }
+      __syncthreads();
     }
   }
-  if (lane == 0) {
+  if (lane == 0 && wv == 0) {
     m[n] = rm;
     s[n] = rs;
   }
@@ -301,9 +316,13 @@ hipError_t launch_vocab_fwd(const uint16_t* x, const uint16_t* w, const int32_t*
         e != hipSuccess)
       return e;
     prof_begin(K_VOC_LSE, s);
-    voc_merge_kernel<<<static_cast<unsigned>(ceil_div(N, 4)), 256, 0, s>>>(
-        reinterpret_cast<const float2*>(part), static_cast<int>(ceil_div(vb, 64)), per, N, m, sm,
-        b0 == 0);
+    const int ng = static_cast<int>(ceil_div(vb, 64));
+    const float2* pairs = reinterpret_cast<const float2*>(part);
+    if (ng <= per || N > (int64_t{1} << 23))  // one block, or rows enough for one wave each
+      voc_merge_kernel<1><<<static_cast<unsigned>(ceil_div(N, 4)), 256, 0, s>>>(pairs, ng, per, N, m,
+                                                                               sm, b0 == 0);
+    else
+      voc_merge_kernel<4><<<static_cast<unsigned>(N), 256, 0, s>>>(pairs, ng, per, N, m, sm, b0 == 0);
     prof_end(K_VOC_LSE, s);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   }
