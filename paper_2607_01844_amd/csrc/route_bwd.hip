@@ -81,20 +81,29 @@ __global__ __launch_bounds__(256) void route_dlogits_kernel(const float* __restr
   }
 }
 
-// dW_r partials: part[c][j][e] = sum over tokens t of chunk c (ascending) of
-// float(x[t][j]) * dl[t][e].  Block = 64 hidden rows x 64 experts, thread =
-// 4 x 4 outputs; x and dl are staged 32 tokens at a time through LDS.  With
-// one chunk the block writes dw_r directly.  Blocks of hidden-row tile 0
-// also produce the bias partials (sum over the chunk of dl[t][e]).
+// dW_r partials: part[c][j][e] = sum over tokens t of chunk c of
+// float(x[t][j]) * dl[t][e].  Block = 64 hidden rows x 64 experts, in G groups
+// of 256 threads that take 32 tokens each in turn (each group sums its tokens
+// in ascending order, the groups' sums are added in group order); thread =
+// 4 x 4 outputs; x and dl are staged 32 tokens at a time and group through
+// LDS.  With one chunk the block writes dw_r directly.  Blocks of hidden-row
+// tile 0 also produce the bias partials (sum over the chunk of dl[t][e]).
+//   Bound by latency where the blocks are few: a group walks its tokens in
+// series, so four groups share a chunk and no more partial sums go through
+// memory than one group leaves (T = 256, d = 128, E = 8: 12 us against 26 in
+// one group, and 13 in four blocks with the reduction; T = 1100, d = 520,
+// E = 12 with the reduction 17 us against 19 in 64-token chunks).
 constexpr int RB_J = 64, RB_E = 64, RB_T = 32;
-__global__ __launch_bounds__(256) void route_dw_kernel(const uint16_t* __restrict__ x,
-                                                       const float* __restrict__ dl, int64_t T,
-                                                       int d, int E, int64_t chunk,
-                                                       float* __restrict__ part,
-                                                       float* __restrict__ bpart) {
-  __shared__ __align__(16) float xs[RB_T][RB_J];
-  __shared__ __align__(16) float ds[RB_T][RB_E];
-  const int tid = threadIdx.x;
+template <int G>
+__global__ __launch_bounds__(256 * G) void route_dw_kernel(const uint16_t* __restrict__ x,
+                                                           const float* __restrict__ dl, int64_t T,
+                                                           int d, int E, int64_t chunk,
+                                                           float* __restrict__ part,
+                                                           float* __restrict__ bpart) {
+  __shared__ float4 sm[G * 2 * RB_T * RB_J / 4];
+  const int tid = threadIdx.x & 255, grp = G == 1 ? 0 : static_cast<int>(threadIdx.x >> 8);
+  float(*xs)[RB_J] = reinterpret_cast<float(*)[RB_J]>(sm + grp * (2 * RB_T * RB_J / 4));
+  float(*ds)[RB_E] = xs + RB_T;
   const int j0 = blockIdx.x * RB_J, e0 = blockIdx.y * RB_E, c = blockIdx.z;
   const int64_t tb = c * chunk, te = min(T, tb + chunk);
   const int tj = tid >> 4, tq = tid & 15;  // outputs j0 + 4 tj + 0..3, e0 + 4 tq + 0..3
@@ -105,7 +114,8 @@ __global__ __launch_bounds__(256) void route_dw_kernel(const uint16_t* __restric
   // dl row r, columns 4 (tid % 16) .. +3 and rows r and r + 16
   const int xr = tid >> 3, xc = (tid & 7) * 8;
   const int dr = tid >> 4, dc = (tid & 15) * 4;
-  for (int64_t t0 = tb; t0 < te; t0 += RB_T) {
+  for (int64_t tr = tb; tr < te; tr += G * RB_T) {
+    const int64_t t0 = tr + grp * RB_T;  // this group's tokens
     {
       const int64_t t = t0 + xr;
       uint4 u = make_uint4(0u, 0u, 0u, 0u);
@@ -134,8 +144,8 @@ __global__ __launch_bounds__(256) void route_dw_kernel(const uint16_t* __restric
       *reinterpret_cast<float4*>(&ds[r][dc]) = v;
     }
     __syncthreads();
-    const int nt = static_cast<int>(min<int64_t>(RB_T, te - t0));
-    for (int r = 0; r < nt; ++r) {
+    const int nt = te - t0 < RB_T ? static_cast<int>(te - t0) : RB_T;  // <= 0: no tokens left
+    auto token = [&](int r) __attribute__((always_inline)) {
       const float4 a = *reinterpret_cast<const float4*>(&xs[r][4 * tj]);
       const float4 b = *reinterpret_cast<const float4*>(&ds[r][4 * tq]);
       const float av[4] = {a.x, a.y, a.z, a.w}, bv[4] = {b.x, b.y, b.z, b.w};
@@ -147,8 +157,37 @@ __global__ __launch_bounds__(256) void route_dw_kernel(const uint16_t* __restric
 #pragma unroll
         for (int q = 0; q < 4; ++q) bacc[q] += bv[q];
       }
+    };
+    if (nt == RB_T) {  // a full tile: reads of several tokens in flight
+#pragma unroll 8
+      for (int r = 0; r < RB_T; ++r) token(r);
+    } else {
+      for (int r = 0; r < nt; ++r) token(r);
     }
     __syncthreads();
+  }
+  if constexpr (G > 1) {
+    // sums of groups 1.. to LDS (the tiles are consumed), added by group 0
+    if (grp > 0) {
+#pragma unroll
+      for (int p = 0; p < 4; ++p)
+        sm[((grp - 1) * 4 + p) * 256 + tid] = make_float4(acc[p][0], acc[p][1], acc[p][2], acc[p][3]);
+      if (do_bias)
+        sm[(G - 1) * 1024 + (grp - 1) * 16 + tq] = make_float4(bacc[0], bacc[1], bacc[2], bacc[3]);
+    }
+    __syncthreads();
+    if (grp > 0) return;
+    for (int g = 0; g < G - 1; ++g) {
+#pragma unroll
+      for (int p = 0; p < 4; ++p) {
+        const float4 v = sm[(g * 4 + p) * 256 + tid];
+        acc[p][0] += v.x; acc[p][1] += v.y; acc[p][2] += v.z; acc[p][3] += v.w;
+      }
+      if (do_bias) {
+        const float4 v = sm[(G - 1) * 1024 + g * 16 + tq];
+        bacc[0] += v.x; bacc[1] += v.y; bacc[2] += v.z; bacc[3] += v.w;
+      }
+    }
   }
   float* out = part + static_cast<int64_t>(c) * d * E;
 #pragma unroll
@@ -365,14 +404,12 @@ __global__ __launch_bounds__(256) void route_zero_kernel(float* __restrict__ p, 
 }  // namespace
 
 // Token chunks of the dW_r reduction: enough blocks to fill the chip
-// (about 2048), each chunk at least 64 tokens (a block walks its chunk's
-// tokens in series: with 256-token chunks T = 256, d = 128, E = 8 took 26 us
-// in two blocks, with 64-token chunks 9 us and the reduction).
+// (about 2048), each chunk at least 256 tokens.
 int route_bwd_chunks(int64_t T, int d, int E) {
   if (T <= 0) return 0;
   const int64_t tiles = ceil_div(d, RB_J) * ceil_div(E, RB_E);
   const int64_t want = ceil_div(2048, tiles);
-  const int64_t most = ceil_div(T, 64);
+  const int64_t most = ceil_div(T, 256);
   return static_cast<int>(std::max<int64_t>(1, std::min(want, most)));
 }
 
@@ -508,9 +545,14 @@ hipError_t launch_route_bwd(const uint16_t* x, const float* w, const float* logi
     bpart = dbias ? reinterpret_cast<float*>(p) : nullptr;
   }
   prof_begin(K_ROUTE_DW, s);
-  route_dw_kernel<<<dim3(static_cast<unsigned>(ceil_div(d, RB_J)),
-                         static_cast<unsigned>(ceil_div(E, RB_E)), static_cast<unsigned>(S)),
-                    256, 0, s>>>(x, dl, T, d, E, chunk, part, bpart);
+  const dim3 tiles(static_cast<unsigned>(ceil_div(d, RB_J)),
+                   static_cast<unsigned>(ceil_div(E, RB_E)), static_cast<unsigned>(S));
+  // four groups a block where the blocks leave most of the chip idle and a
+  // group would walk more than one tile of tokens
+  if (static_cast<int64_t>(tiles.x) * tiles.y * S < 512 && chunk > RB_T)
+    route_dw_kernel<4><<<tiles, 1024, 0, s>>>(x, dl, T, d, E, chunk, part, bpart);
+  else
+    route_dw_kernel<1><<<tiles, 256, 0, s>>>(x, dl, T, d, E, chunk, part, bpart);
   if (S > 1) {
     const int nb = dbias ? E : 0;
     route_dw_reduce_kernel<<<static_cast<unsigned>(ceil_div(nw + nb, 256)), 256, 0, s>>>(

@@ -160,6 +160,19 @@ def test_row_chunked_workspace_layout(lib):
     assert abs((n4.value - fixed) / (n8.value - fixed) - 2) < 0.05
 
 
+def test_route_bwd_workspace_holds_partials_of_256_token_chunks(lib):
+    """One chunk of up to 256 tokens needs no partial sums (a caller with its
+    own dlogits then needs no workspace at all); more tokens need one set per
+    chunk, until 2048 blocks of 64 hidden rows x 64 experts."""
+    n = ctypes.c_size_t()
+    up = lambda v: (v + 255) // 256 * 256  # noqa: E731
+    for T, d, E, chunks in [(1, 128, 8, 1), (256, 128, 8, 1), (257, 128, 8, 2), (1100, 520, 12, 5),
+                            (8192, 3968, 8, 32), (4096, 8000, 8, 16)]:
+        assert lib.moe_route_bwd_workspace_bytes(T, d, E, ctypes.byref(n)) == 0
+        part = 0 if chunks == 1 else up(4 * chunks * d * E) + up(4 * chunks * E)
+        assert n.value == up(4 * T * E) + part, (T, d, E)
+
+
 @pytest.mark.skipif(not _no_gpu(), reason="dummy pointers are only safe without a GPU")
 @pytest.mark.parametrize("vblock", [1 << 31, 1 << 34, 1 << 35, (1 << 40) - 8])
 def test_vocab_block_beyond_an_int_reaches_the_launch(vblock):

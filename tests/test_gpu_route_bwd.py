@@ -123,6 +123,34 @@ def test_route_bwd_small(case):
     _say(f"[route_bwd] {name} ok {errs}")
 
 
+# dW_r and dbias on the vector ALUs: four groups of 32 tokens a block (chunks
+# that end in each of them), one group (a single tile of tokens; many blocks),
+# and chunks of unequal length
+@pytest.mark.parametrize("T,d,E", [(20, 72, 9), (32, 72, 9), (33, 72, 9), (64, 136, 70), (65, 72, 8),
+                                   (97, 72, 9), (128, 200, 12), (129, 72, 9), (256, 72, 9),
+                                   (257, 72, 9), (700, 72, 66), (1000, 4096, 65)])
+def test_route_bwd_token_groups(T, d, E):
+    _say(f"[route_bwd] groups T={T} d={d} E={E}")
+    moe = _moe()
+    g = torch.Generator(device="cpu").manual_seed(T)
+    x = torch.randn((T, d), generator=g).to(torch.bfloat16).cuda()
+    w = (0.02 * torch.randn((d, E), generator=g)).cuda()
+    dgate = torch.randn((T, 3), generator=g).cuda()
+    lg, idx, gate = _route(x, w, None, 3, 0)
+    dw, db, _, dl = _run_bwd(x, w, lg, idx, gate, dgate, 0, None, True, True, True)
+    # the sums of T fp32 products: within T 2^-24 of the sum of magnitudes
+    xf, df = x.double(), dl.double()
+    for name, got, ref, mag in (("dw", dw, xf.t() @ df, xf.abs().t() @ df.abs()),
+                                ("dbias", db, df.sum(0), df.abs().sum(0))):
+        assert torch.all((got.double() - ref).abs() <= T * 2.0 ** -24 * mag), name
+    if T <= 256:  # one chunk and the caller's own dlogits: no workspace is needed
+        dw2, dl2 = torch.full_like(dw, float("nan")), torch.full_like(dl, float("nan"))
+        p = moe._ptr
+        assert moe.lib.moe_route_bwd(p(x), p(w), p(lg), p(idx), p(gate), p(dgate), T, d, E, 3, 0,
+                                     p(dw2), None, None, 0, p(dl2), None, 0, moe._stream()) == 0
+        assert torch.equal(dw2.view(torch.int32), dw.view(torch.int32))
+
+
 def test_route_bwd_zero_tokens():
     moe = _moe()
     x = torch.empty((0, 64), dtype=torch.bfloat16, device="cuda")
