@@ -73,14 +73,18 @@ def workspace(nbytes: int, device, tag: str) -> torch.Tensor:
     current stream, tag): calls on one stream are ordered, calls on different
     streams get different buffers.  A buffer replaced by a larger one is
     kept alive until the process ends, so a HIP graph captured with it never
-    replays into freed memory (capture with the sizes it will replay)."""
-    index = device.index if device.index is not None else torch.cuda.current_device()
+    replays into freed memory (capture with the sizes it will replay).
+    device: a torch.device, or what names one (text or number)."""
+    if type(device) is torch.device and device.type == "cuda":
+        index = device.index if device.index is not None else torch.cuda.current_device()
+    else:
+        index = torch.cuda.current_stream(device).device.index  # refuses what is no GPU
     key = (index, _raw_stream(index), tag)
     buf = _ws_cache.get(key)
     if buf is None or buf.numel() < nbytes:
         if buf is not None:
             _ws_retired.append(buf)
-        buf = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=device)
+        buf = torch.empty(max(int(nbytes), 256), dtype=torch.uint8, device=f"cuda:{index}")
         _ws_cache[key] = buf
     return buf
 
