@@ -79,6 +79,8 @@ SMALL = [
     ("mfma_ragged", 2100, 1032, 128, 4, 1, False, False, True, False),
     # E not a multiple of 8 (padded columns of the split logit gradients)
     ("mfma_E100", 2624, 1024, 100, 4, 0, True, True, True, True),
+    # both products on 256-row tiles (the ones above run 128-row tiles)
+    ("mfma_large", 8100, 2000, 250, 4, 0, True, True, True, True),
 ]
 
 
@@ -86,6 +88,12 @@ SMALL = [
 def test_route_bwd_small(case):
     name, T, d, E, k, renorm, use_bias, acc, with_db, want_dl = case
     _say(f"[route_bwd] {name} T={T} d={d} E={E} k={k} renorm={renorm}")
+    if name.startswith("mfma"):
+        up = lambda a, b: -(-a // b)  # noqa: E731
+        tiles = up(d, 256) * up(E, 128)
+        chunks = min(up(512, tiles), up(T, 512))  # token chunks of dW_r
+        for n in (up(T, up(up(T, chunks), 64) * 64) * tiles, up(T, 256) * up(d, 256)):
+            assert P.large_tile(n) == (name == "mfma_large"), n
     g = torch.Generator(device="cpu").manual_seed(11)
     x = torch.randn((T, d), generator=g).to(torch.bfloat16).cuda()
     w = (0.02 * torch.randn((d, E), generator=g)).cuda()

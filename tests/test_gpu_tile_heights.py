@@ -15,18 +15,26 @@ COUNTS = {
     "one_tile": [1, 31, 32, 33, 64, 65, 96, 97, 128, 129, 160, 161, 192, 193, 224, 225, 255, 256],
     "two_tiles": [257, 0, 288, 320, 321, 352, 384, 385, 416, 448, 480, 511, 512],
     "three_tiles": [513, 576, 577, 0, 0, 640, 672, 704, 767, 768, 769],
+    # up to 63 experts the 128-row launches form their tables in registers
+    "experts_62": [(7 * i) % 43 for i in range(62)],
+    "experts_63": [0] + [(7 * i) % 43 for i in range(62)],
+    "experts_64": [(7 * i) % 43 for i in range(63)] + [40],
+    "experts_65": [(7 * i) % 43 for i in range(63)] + [0, 300],
 }
 
 
 @pytest.mark.parametrize("name", list(COUNTS))
-# the 128-row tile (few tiles in all), and with f = 5128 the 256-row tile
-# (more than two tiles per compute unit)
+# forward and data gradients on the 128-row tile (few tiles in all), on it up
+# to 18 experts, and on the 256-row tile (more than two tiles per compute unit)
 @pytest.mark.parametrize("d,f", [(72, 136), (264, 328), (72, 5128)])
 def test_rows_around_tile_heights(name, d, f):
     from paper_2607_01844_amd import moe
     counts = COUNTS[name]
     print(f"[tile heights] {name} d={d} f={f}", flush=True)
     E, M = len(counts), sum(counts)
+    up = lambda a, b: -(-a // b)  # noqa: E731
+    for n in (max(up(f, 128), up(d, 256)), max(up(f, 256), up(d, 256))):  # forward, data gradients
+        assert P.large_tile((min(M, E) + M // 256) * n, M, E) == (f == 5128 or (f == 328 and E > 18))
     off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
     gen = torch.Generator().manual_seed(M + d)
     r = lambda *s, std=1.0: (torch.randn(s, generator=gen) * std).to(torch.bfloat16)  # noqa: E731

@@ -1,5 +1,5 @@
-"""Vocabulary loss where its products take the 256-row tile and the ping-pong
-weight gradient, with rows of W and dW of every alignment, and the forward
+"""Vocabulary loss where every product of its first block takes the 256-row
+tile, and dW the ping-pong schedule, with rows of W and dW of every alignment, and the forward
 over one block at a time (a workspace that holds the forward's buffers only)
 bit for bit against the forward over many."""
 import ctypes
@@ -21,7 +21,12 @@ def _inputs(N, H, V, seed):
 @pytest.mark.parametrize("V", [17003, 17000, 16390])
 def test_large_tiles_any_row_alignment(V):
     from paper_2607_01844_amd import moe
-    N, H, vb = 1100, 1024, 16384
+    N, H, vb = 2040, 1000, 16384
+    rows, cols = 8, 4  # 256-row tiles over N and H
+    assert P.large_tile(rows * -(-V // 256))       # forward (all of V at once)
+    assert P.large_tile(rows * (vb // 256))        # logit gradients
+    assert P.large_tile(8 * rows * cols)           # dx, in 8 ranges of the block
+    assert P.large_tile(cols * (vb // 256)) and N >= 16 * 64  # dW, ping-pong
     print(f"[vocab span] N={N} H={H} V={V}", flush=True)
     i = _inputs(N, H, V, V)
     dw = torch.full((H, V), float("nan"), dtype=torch.bfloat16, device="cuda")
