@@ -95,19 +95,26 @@ hipError_t run_gemm(const GemmArgs& a, bool small, int kid, hipStream_t s) {
 
 // The 128-row tile where 256-row tiles would use less than two thirds of the
 // CUs over their rounds (a full chip runs the large tile about 1.5 times as
-// fast, since it reads its operands half as often), or at most 16 rows per
-// expert on average, where a product is its weights' stream and two
-// workgroups a CU keep more of it in flight.  Both sides measured (whole
+// fast, since it reads its operands half as often).  Both sides measured (whole
 // passes, 256- against 128-row tiles): 12 experts of 275 rows, d = 520, f =
 // 328 (75 tiles) 251 -> 191 us a training step; the vocabulary loss in blocks
-// of 64 tiles 987 -> 610 us; 64 experts of up to 16 rows, d = 2048 240 -> 220
-// us; and beyond the lines the vocabulary loss in products of 512 tiles 12.2
-// -> 13.6 ms, 128 experts of 62 rows, d = 4096 1043 -> 1194 us, mid's training
-// step (1408 tiles) 1830 -> 2164 us, its weight gradients alone 1830 -> 1964.
-bool use_small(int64_t tiles, int64_t rows, int64_t experts) {
+// of 64 tiles 987 -> 610 us; and beyond the line the vocabulary loss in
+// products of 512 tiles 12.2 -> 13.6 ms, mid's training step (1408 tiles) 1830
+// -> 2164 us, its weight gradients alone 1830 -> 1964.  The row-grouped
+// products count capacity, not rows: a bound that costs no wait, and above the
+// real tile count where experts or rows are absent.
+bool use_small(int64_t tiles) {
   const int64_t cus = device_cus();
-  return 3 * tiles < 2 * cus * ceil_div(tiles, cus) || rows <= 16 * experts;
+  return 3 * tiles < 2 * cus * ceil_div(tiles, cus);
 }
+// The forward and the data gradients take it too at 16 rows per expert or
+// fewer on average, where a product is its weights' stream and two workgroups
+// a CU keep more of it in flight (64 experts of 8 rows, d = 2048, f = 1408:
+// down 78 -> 70 us, data gradients 261 -> 201; 128 experts of 62 rows, d =
+// 4096 1043 -> 1194 us a forward).  The weight gradients do not: there they
+// write far more than they read, in pieces half as long (the same 64 experts
+// 306 us against 357, 128 of 8 rows, d = 4096, f = 1536 1107 against 1420).
+bool few_rows(int64_t rows, int64_t experts) { return rows <= 16 * experts; }
 // Upper bound of the row tiles of E_loc experts with up to cap rows in all.
 int64_t row_tiles(int64_t cap, int E_loc) { return std::min<int64_t>(cap, E_loc) + cap / TILE; }
 
@@ -133,7 +140,8 @@ hipError_t launch_ffn_fwd(const uint16_t* x_perm, const int32_t* offsets, int E_
                           void* ws, hipStream_t s) {
   GemmWs w = carve(ws, cap, E_loc, f, false);
   const int64_t rt = row_tiles(cap, E_loc);
-  const bool small = use_small(rt * std::max(ceil_div(f, TILE / 2), ceil_div(d, TILE)), cap, E_loc);
+  const bool small =
+      use_small(rt * std::max(ceil_div(f, TILE / 2), ceil_div(d, TILE))) || few_rows(cap, E_loc);
   const int S = small ? TILE_S : TILE;
   if (small && E_loc <= REG_EXPERTS) w.mt_start = nullptr;  // the kernels form the tables
   else if (hipError_t e = sched(offsets, E_loc, S, w, s); e != hipSuccess) return e;
@@ -156,12 +164,13 @@ hipError_t launch_ffn_bwd(const uint16_t* dy, const uint16_t* x_perm, const uint
                           uint16_t* dwd, unsigned flags, void* ws, hipStream_t s) {
   GemmWs w = carve(ws, cap, E_loc, f, true);
   const int64_t rt = row_tiles(cap, E_loc);
-  const bool small = use_small(rt * std::max(ceil_div(f, TILE), ceil_div(d, TILE)), cap, E_loc);
+  const bool small =
+      use_small(rt * std::max(ceil_div(f, TILE), ceil_div(d, TILE))) || few_rows(cap, E_loc);
   const int S = small ? TILE_S : TILE;
   const int64_t experts = std::min<int64_t>(cap, E_loc);
   const bool wgrad = (flags & MOE_BWD_WGRAD) != 0;
-  const bool small_g = use_small(experts * ceil_div(d, TILE) * ceil_div(f, TILE / 2), cap, E_loc);
-  const bool small_d = use_small(experts * ceil_div(f, TILE) * ceil_div(d, TILE), cap, E_loc);
+  const bool small_g = use_small(experts * ceil_div(d, TILE) * ceil_div(f, TILE / 2));
+  const bool small_d = use_small(experts * ceil_div(f, TILE) * ceil_div(d, TILE));
   if (small && (!wgrad || (small_g && small_d)) && E_loc <= REG_EXPERTS)
     w.mt_start = nullptr;  // the kernels form the tables
   else if (hipError_t e = sched(offsets, E_loc, S, w, s); e != hipSuccess)
@@ -210,7 +219,7 @@ hipError_t run_dense(GemmArgs& a, int kid, hipStream_t s) {
   };
   const int64_t n = tiles(TILE);
   if (n <= 0) return hipSuccess;
-  const bool small = use_small(n, 1, 0);
+  const bool small = use_small(n);
   if (small) tiles(TILE_S);
   return run_gemm<MODE>(a, small, kid, s);
 }

@@ -18,9 +18,10 @@ def bits(t):
 
 
 def large_tile(tiles, rows=1, experts=0):
-    """Whether a grouped GEMM launch of `tiles` 256-row tiles (`rows` rows over
-    `experts` experts; dense products: neither) runs them, and not 128-row
-    tiles: the launch's own rule, for tests that cover one tile or the other."""
+    """Whether a grouped GEMM launch of `tiles` 256-row tiles (forward and data
+    gradients: of `rows` rows over `experts` experts) runs them, and not
+    128-row tiles: the launch's own rule, for tests that cover one or the
+    other."""
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     return 3 * tiles >= 2 * cus * -(-tiles // cus) and rows > 16 * experts
 

@@ -123,7 +123,7 @@ def test_small_full_parity(name):
         # such expert)
         up = lambda a, b: -(-a // b)  # noqa: E731
         for tiles in (up(wl.d, 256) * up(wl.f, 128), up(wl.f, 256) * up(wl.d, 256)):
-            assert P.large_tile(wl.E * tiles, wl.cap, wl.E), tiles
+            assert P.large_tile(wl.E * tiles), tiles
         n = np.diff(gpu["expert_offsets"].cpu().numpy().astype(np.int64))
         steps = (n + 63) // 64
         assert steps.sum() >= 16 * (n > 0).sum(), (steps.sum(), (n > 0).sum())

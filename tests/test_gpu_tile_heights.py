@@ -20,6 +20,10 @@ COUNTS = {
     "experts_63": [0] + [(7 * i) % 43 for i in range(62)],
     "experts_64": [(7 * i) % 43 for i in range(63)] + [40],
     "experts_65": [(7 * i) % 43 for i in range(63)] + [0, 300],
+    # few rows an expert: 128-row forward and data gradients beside (f = 5128)
+    # 256-row weight gradients, both sides of the in-register tables
+    "few_rows_60": [i % 9 for i in range(60)],
+    "few_rows_70": [130] + [i % 9 for i in range(69)],
 }
 
 
@@ -35,7 +39,9 @@ def test_rows_around_tile_heights(name, d, f):
     up = lambda a, b: -(-a // b)  # noqa: E731
     for n in (max(up(f, 128), up(d, 256)), max(up(f, 256), up(d, 256))):  # forward, data gradients
         if f != 328:
-            assert P.large_tile((min(M, E) + M // 256) * n, M, E) == (f == 5128)
+            assert P.large_tile((min(M, E) + M // 256) * n, M, E) == (f == 5128 and M > 16 * E)
+        if M <= 16 * E and f == 5128:  # the weight gradients
+            assert P.large_tile(min(M, E) * up(f, 128)) and P.large_tile(min(M, E) * up(f, 256))
     off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
     gen = torch.Generator().manual_seed(M + d)
     r = lambda *s, std=1.0: (torch.randn(s, generator=gen) * std).to(torch.bfloat16)  # noqa: E731
