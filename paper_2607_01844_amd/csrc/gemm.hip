@@ -10,17 +10,17 @@ using namespace gemm;
 namespace {
 
 // Per-expert prefixes over experts in index order: tiles of up to `rows` rows
-// (mt_start), K
-// steps (wk_start) and experts with rows (nz_start).  One workgroup,
-// E_loc <= 1024.
+// (mt_start), K steps, or other tiles, of up to `krows` rows (wk_start) and
+// experts with rows (nz_start).  One workgroup, E_loc <= 1024.
 __global__ __launch_bounds__(1024) void gemm_sched_kernel(const int32_t* __restrict__ offsets,
-                                                          int E_loc, int rows, int32_t* __restrict__ mt_start,
+                                                          int E_loc, int rows, int krows,
+                                                          int32_t* __restrict__ mt_start,
                                                           int32_t* __restrict__ wk_start,
                                                           int32_t* __restrict__ nz_start) {
   __shared__ int wsum[3][16];
   const int e = threadIdx.x;
   const int n = (e < E_loc) ? offsets[e + 1] - offsets[e] : 0;
-  const int v[3] = {(n + rows - 1) / rows, (n + BK - 1) / BK, n > 0 ? 1 : 0};
+  const int v[3] = {(n + rows - 1) / rows, (n + krows - 1) / krows, n > 0 ? 1 : 0};
   int32_t* const out[3] = {mt_start, wk_start, nz_start};
   const int lane = e & 63, w = e >> 6;
   int incl[3] = {v[0], v[1], v[2]};
@@ -107,8 +107,8 @@ bool use_small(int64_t tiles) {
   const int64_t cus = device_cus();
   return 3 * tiles < 2 * cus * ceil_div(tiles, cus);
 }
-// The forward and the data gradients take it too at 16 rows per expert or
-// fewer on average, where a product is its weights' stream and two workgroups
+// The forward (its gate/up product up to d = 2048) and the data gradients take
+// it too at 16 rows per expert or fewer on average, where a product is its weights' stream and two workgroups
 // a CU keep more of it in flight (64 experts of 8 rows, d = 2048, f = 1408:
 // down 78 -> 70 us, data gradients 261 -> 201; 128 experts of 62 rows, d =
 // 4096 1043 -> 1194 us a forward).  The weight gradients do not: there they
@@ -118,9 +118,11 @@ bool few_rows(int64_t rows, int64_t experts) { return rows <= 16 * experts; }
 // Upper bound of the row tiles of E_loc experts with up to cap rows in all.
 int64_t row_tiles(int64_t cap, int E_loc) { return std::min<int64_t>(cap, E_loc) + cap / TILE; }
 
-hipError_t sched(const int32_t* offsets, int E_loc, int rows, const GemmWs& w, hipStream_t s) {
+hipError_t sched(const int32_t* offsets, int E_loc, int rows, int krows, const GemmWs& w,
+                 hipStream_t s) {
   prof_begin(K_GEMM_SCHED, s);
-  gemm_sched_kernel<<<1, 1024, 0, s>>>(offsets, E_loc, rows, w.mt_start, w.wk_start, w.nz_start);
+  gemm_sched_kernel<<<1, 1024, 0, s>>>(offsets, E_loc, rows, krows, w.mt_start, w.wk_start,
+                                       w.nz_start);
   prof_end(K_GEMM_SCHED, s);
   return hipGetLastError();
 }
@@ -140,21 +142,38 @@ hipError_t launch_ffn_fwd(const uint16_t* x_perm, const int32_t* offsets, int E_
                           void* ws, hipStream_t s) {
   GemmWs w = carve(ws, cap, E_loc, f, false);
   const int64_t rt = row_tiles(cap, E_loc);
-  const bool small =
-      use_small(rt * std::max(ceil_div(f, TILE / 2), ceil_div(d, TILE))) || few_rows(cap, E_loc);
-  const int S = small ? TILE_S : TILE;
-  if (small && E_loc <= REG_EXPERTS) w.mt_start = nullptr;  // the kernels form the tables
-  else if (hipError_t e = sched(offsets, E_loc, S, w, s); e != hipSuccess) return e;
+  const bool idle = use_small(rt * std::max(ceil_div(f, TILE / 2), ceil_div(d, TILE)));
+  const bool few = few_rows(cap, E_loc);
+  // gate/up, down: the gate/up product's weights lie along f, so its 128-row
+  // tile reads them in pieces half as long, which costs more than the second
+  // workgroup brings once its loop over d is long (256- against 128-row tiles:
+  // 128 experts of 8 rows, d = 4096, f = 1536 585 us against 690, 64 of 8, d =
+  // 3072 257 against 298, 32 of 8, d = 7168, f = 2048 364 against 435; d =
+  // 2048 even to 7 % slower, where few experts have rows)
+  const bool small = idle || (few && d <= 2048), small_d = idle || few;
+  int32_t* mt_down = w.mt_start;
+  if (small && E_loc <= REG_EXPERTS) {
+    w.mt_start = mt_down = nullptr;  // the kernels form the tables
+  } else {
+    // no product of the forward counts K steps: their table holds the 128-row
+    // tiles where only the down product takes those
+    const bool both = small != small_d;
+    if (both) mt_down = w.wk_start;
+    if (hipError_t e = sched(offsets, E_loc, small ? TILE_S : TILE, both ? TILE_S : BK, w, s);
+        e != hipSuccess)
+      return e;
+  }
   GemmArgs a{};
   a.x_perm = x_perm; a.wg = wg; a.wu = wu; a.wd = wd;
   a.offsets = offsets; a.mt_start = w.mt_start; a.wk_start = w.wk_start; a.nz_start = w.nz_start;
   a.hg = hg; a.hu = hu; a.act = w.act; a.act_in = w.act; a.y = y;
   a.E_loc = E_loc; a.d = d; a.f = f;
-  a.NT = static_cast<int>(ceil_div(f, S / 2));
+  a.NT = static_cast<int>(ceil_div(f, (small ? TILE_S : TILE) / 2));
   if (hipError_t e = run_gemm<FWD_GATE_UP>(a, small, K_GEMM_FWD_GATE_UP, s); e != hipSuccess)
     return e;
-  a.NT = static_cast<int>(ceil_div(d, S));
-  return run_gemm<FWD_DOWN>(a, small, K_GEMM_FWD_DOWN, s);
+  a.mt_start = mt_down;
+  a.NT = static_cast<int>(ceil_div(d, small_d ? TILE_S : TILE));
+  return run_gemm<FWD_DOWN>(a, small_d, K_GEMM_FWD_DOWN, s);
 }
 
 hipError_t launch_ffn_bwd(const uint16_t* dy, const uint16_t* x_perm, const uint16_t* hg,
@@ -173,7 +192,7 @@ hipError_t launch_ffn_bwd(const uint16_t* dy, const uint16_t* x_perm, const uint
   const bool small_d = use_small(experts * ceil_div(f, TILE) * ceil_div(d, TILE));
   if (small && (!wgrad || (small_g && small_d)) && E_loc <= REG_EXPERTS)
     w.mt_start = nullptr;  // the kernels form the tables
-  else if (hipError_t e = sched(offsets, E_loc, S, w, s); e != hipSuccess)
+  else if (hipError_t e = sched(offsets, E_loc, S, BK, w, s); e != hipSuccess)
     return e;
   GemmArgs a{};
   a.x_perm = x_perm; a.wg = wg; a.wu = wu; a.wd = wd;

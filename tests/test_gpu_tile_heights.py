@@ -27,10 +27,13 @@ COUNTS = {
 }
 
 
-@pytest.mark.parametrize("name", list(COUNTS))
 # forward and data gradients on the 128-row tile (few tiles in all), on either,
-# and on the 256-row tile (more than two tiles per compute unit)
-@pytest.mark.parametrize("d,f", [(72, 136), (264, 328), (72, 5128)])
+# and on the 256-row tile (more than two tiles per compute unit); with few rows
+# an expert and d > 2048 the 256-row gate/up product beside the 128-row down
+# product, whose tile counts differ (an expert of 130 rows)
+@pytest.mark.parametrize("name,d,f", [(n, *df) for df in [(72, 136), (264, 328), (72, 5128)]
+                                      for n in COUNTS] + [("few_rows_60", 2056, 136),
+                                                          ("few_rows_70", 2056, 136)])
 def test_rows_around_tile_heights(name, d, f):
     from paper_2607_01844_amd import moe
     counts = COUNTS[name]
@@ -38,7 +41,9 @@ def test_rows_around_tile_heights(name, d, f):
     E, M = len(counts), sum(counts)
     up = lambda a, b: -(-a // b)  # noqa: E731
     for n in (max(up(f, 128), up(d, 256)), max(up(f, 256), up(d, 256))):  # forward, data gradients
-        if f != 328:
+        if d == 2056:
+            assert M <= 16 * E and P.large_tile((min(M, E) + M // 256) * n)
+        elif f != 328:
             assert P.large_tile((min(M, E) + M // 256) * n, M, E) == (f == 5128 and M > 16 * E)
         if M <= 16 * E and f == 5128:  # the weight gradients
             assert P.large_tile(min(M, E) * up(f, 128)) and P.large_tile(min(M, E) * up(f, 256))
