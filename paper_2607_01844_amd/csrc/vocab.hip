@@ -43,14 +43,19 @@ __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2
 // pairs in order (lane l takes groups l, l + 64, ... ascending, then a fixed
 // xor tree over the lanes); the blocks' pairs then go into the row's running
 // pair (m, s) in order, so the result does not depend on how many blocks a
-// launch takes.  Bound by latency (loads, then twelve dependent shuffles and
-// exponentials a block): with several blocks four waves share a row, two
-// blocks each at a time (N = 1000, H = 520, V = 32003 in blocks of 4096, loss
-// and gradients: 497 us against 503 with one wave a row).
+// launch takes.  The last launch turns the row's pair into its results:
+// lse_n = m_n + log s_n, loss_n = y_{n, t_n} - lse_n.  Bound by latency (loads,
+// then twelve dependent shuffles and exponentials a block): with several
+// blocks four waves share a row, two blocks each at a time (N = 1000, H = 520,
+// V = 32003 in blocks of 4096, loss and gradients: 497 us against 500 with one
+// wave a row, and 499 with the results in a launch of their own).
 template <int W>
 __global__ __launch_bounds__(256) void voc_merge_kernel(const float2* __restrict__ part, int ng,
                                                         int per, int64_t N, float* __restrict__ m,
-                                                        float* __restrict__ s, int first) {
+                                                        float* __restrict__ s, int first, int last,
+                                                        const float* __restrict__ yt,
+                                                        float* __restrict__ loss,
+                                                        float* __restrict__ lse) {
   constexpr int U = W == 1 ? 1 : 2;
   __shared__ float2 blk[W == 1 ? 1 : U * W];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wv = wave % W;
@@ -109,22 +114,15 @@ __global__ __launch_bounds__(256) void voc_merge_kernel(const float2* __restrict
     }
   }
   if (lane == 0 && wv == 0) {
-    m[n] = rm;
-    s[n] = rs;
+    if (last) {
+      const float l = rm + logf(rs);
+      lse[n] = l;
+      loss[n] = yt[n] - l;
+    } else {
+      m[n] = rm;
+      s[n] = rs;
+    }
   }
-}
-
-// loss_n = y_{n, t_n} - lse_n, lse_n = m_n + log s_n
-__global__ __launch_bounds__(256) void voc_finalize_kernel(const float* __restrict__ m,
-                                                           const float* __restrict__ s,
-                                                           const float* __restrict__ yt, int64_t N,
-                                                           float* __restrict__ loss,
-                                                           float* __restrict__ lse) {
-  const int64_t n = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (n >= N) return;
-  const float l = m[n] + logf(s[n]);
-  lse[n] = l;
-  loss[n] = yt[n] - l;
 }
 
 // dx[i] = bf16(sum over slabs b ascending of dxa[b][i]), 8 values per thread
@@ -318,17 +316,17 @@ hipError_t launch_vocab_fwd(const uint16_t* x, const uint16_t* w, const int32_t*
     prof_begin(K_VOC_LSE, s);
     const int ng = static_cast<int>(ceil_div(vb, 64));
     const float2* pairs = reinterpret_cast<const float2*>(part);
+    const int first = b0 == 0, last = b0 + span >= V;
     if (ng <= per || N > (int64_t{1} << 23))  // one block, or rows enough for one wave each
-      voc_merge_kernel<1><<<static_cast<unsigned>(ceil_div(N, 4)), 256, 0, s>>>(pairs, ng, per, N, m,
-                                                                               sm, b0 == 0);
+      voc_merge_kernel<1><<<static_cast<unsigned>(ceil_div(N, 4)), 256, 0, s>>>(
+          pairs, ng, per, N, m, sm, first, last, yt, loss, lse);
     else
-      voc_merge_kernel<4><<<static_cast<unsigned>(N), 256, 0, s>>>(pairs, ng, per, N, m, sm, b0 == 0);
+      voc_merge_kernel<4><<<static_cast<unsigned>(N), 256, 0, s>>>(pairs, ng, per, N, m, sm, first,
+                                                                   last, yt, loss, lse);
     prof_end(K_VOC_LSE, s);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   }
-  voc_finalize_kernel<<<static_cast<unsigned>(ceil_div(N, 256)), 256, 0, s>>>(m, sm, yt, N, loss,
-                                                                              lse);
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 hipError_t launch_vocab_bwd(const uint16_t* x, const uint16_t* w, const int32_t* target,
