@@ -108,10 +108,10 @@ bool use_small(int64_t tiles) {
   return 3 * tiles < 2 * cus * ceil_div(tiles, cus);
 }
 // The forward (its gate/up product up to d = 2048) and the data gradients take
-// it too at 16 rows per expert or fewer on average, where a product is its weights' stream and two workgroups
-// a CU keep more of it in flight (64 experts of 8 rows, d = 2048, f = 1408:
-// down 78 -> 70 us, data gradients 261 -> 201; 128 experts of 62 rows, d =
-// 4096 1043 -> 1194 us a forward).  The weight gradients do not: there they
+// it too at 16 rows per expert or fewer on average, where a product is its
+// weights' stream and two workgroups a CU keep more of it in flight (64 experts
+// of 8 rows, d = 2048, f = 1408: down 78 -> 70 us, data gradients 261 -> 201;
+// beyond the line 128 experts of 62 rows, d = 4096: 1043 -> 1194 us a forward).  The weight gradients do not: there they
 // write far more than they read, in pieces half as long (the same 64 experts
 // 306 us against 357, 128 of 8 rows, d = 4096, f = 1536 1107 against 1420).
 bool few_rows(int64_t rows, int64_t experts) { return rows <= 16 * experts; }

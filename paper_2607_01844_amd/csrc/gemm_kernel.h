@@ -9,7 +9,8 @@
 //     every global store moves 16 bytes per lane.
 //   * A second tile size, 128 x 128 with 256 threads in a 2 x 2 grid (64 rows
 //     x 64 columns each) and 16 KiB ring slots, two workgroups a CU, runs the
-//     launches that 256-row tiles would leave most of the chip idle for.
+//     launches whose 256-row tiles would leave more than a third of the chip
+//     idle, and those that stream weights for few rows per expert.
 //     Sizes below are those of the 256-row tile.
 //   * Operands move global -> LDS with buffer_load_dwordx4 ... lds (no
 //     register staging).  Out-of-range lanes (rows past an expert's segment,
@@ -483,25 +484,27 @@ __device__ __forceinline__ uint2 pack4(float a, float b, float c, float d) {
 }
 
 
-// One output tile of one expert.  h = its height in 32-row blocks (8 unless
-// the mode takes the rows in equal tiles: tile_blocks below).
+// One output tile of one expert.  h = its height in 32-row blocks (S / 32
+// unless the mode takes the rows in equal tiles: tile_blocks below).
 struct Tile {
   bool valid;
   int e, m0, n0, seg, ne, nk, h;
 };
 
-// Height, in blocks of 32 rows, of the mt = ceil(rows / 256) tiles that `rows`
+// Height, in blocks of 32 rows, of the mt = ceil(rows / S) tiles that `rows`
 // rows are cut into: equal tiles instead of full ones and a rest, so that
-// padding costs at most 31 rows a tile and no compute unit gets only full
-// tiles while another gets only rests.  At least two blocks (one per wave
-// row).  384 rows: two tiles of 192 (6 blocks) instead of two of 256.
+// padding costs fewer than 32 rows a tile on average and no compute unit gets
+// only full tiles while another gets only rests.  At least two blocks (one per
+// wave row), so an expert of 32 rows or fewer is padded to 64.  384 rows: two
+// 256-row tiles become two of 192 (6 blocks).
 // Measured against full tiles: the four row-grouped products of 32 experts of
 // 339 rows (d = 7168, f = 2048) 2415 -> 1930 us together, of 64 experts of
 // 384 rows (d = 2048, f = 1408) 1125 -> 1060 us.
 __device__ __forceinline__ int tile_blocks(int rows, int mt) { return max(2, (rows + 32 * mt - 1) / (32 * mt)); }
 
 // The sequence of tiles one workgroup computes.  The grid has one workgroup
-// per CU; workgroup b runs on XCD b % 8 as CU slot b / 8 of that XCD.
+// per CU (256-row tile) or two (128-row tile); workgroup b runs on XCD b % 8
+// as slot b / 8 of that XCD ("CU" below: such a slot).
 //  * Row-grouped GEMMs: logical tiles (expert-major; inside an expert the
 //    row tiles of one column tile are adjacent) are cut into 8 equal
 //    contiguous ranges, one per XCD, dealt round-robin to the XCD's CUs.
