@@ -41,12 +41,12 @@ __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
-// Bound by the fp32 matrix cores where the tiles fill the chip (long,
-// T = 65536, d = 4096, E = 128: 556 us = 124 TFLOP/s of 157; the vector-ALU
-// chains it replaces took 1160 us; T = 16384, d = 7168, E = 384: 1416 -> 750
-// us), by one wave's chain of d / 4 dependent instructions where they do not
-// (T = 1000, d = 4096, E = 128: 105 -> 38 us; T = 16, d = 2048, E = 64: 38 ->
-// 18 us).
+// Bound by the fp32 matrix cores where the tiles fill the chip (T = 65536, d =
+// 4096, E = 128: 624 us = 110 TFLOP/s of 157; the vector-ALU chains it replaces
+// took 1365 us; T = 16384, d = 7168, E = 384: 1538 -> 811 us, and 910 on
+// average among a layer's other kernels), by one wave's chain of d / 4
+// dependent instructions where they do not (T = 1000, d = 4096, E = 128: 95 ->
+// 33 us; T = 16, d = 2048, E = 64: 36 -> 18 us).
 // Block = GT x GE waves, each WT x WE tiles of 16 tokens x 16 experts (one
 // v_mfma_f32_16x16x4_f32 accumulator each: A = x, lane l row l % 16 and
 // k = l / 16; B = W_r, lane l column l % 16 and k = l / 16).  Chunks of KC
