@@ -474,9 +474,15 @@ __device__ __forceinline__ void store_any(uint16_t* to, const uint4& v, int n) {
 // operand slabs out of the 4 MiB L2s: gate/up data gradient of mid 309 -> 301
 // us, of long 12.6 -> 12.3 ms, and the combine that follows 29.7 -> 25 us at
 // mid.  (The other outputs gain nothing or lose: 64-byte pieces, gate/up
-// weight gradient of mid 389 -> 430 us.)
-__device__ __forceinline__ void store_nt(uint16_t* to, const uint4& v) {
-  __builtin_nontemporal_store(u32x4a{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4a*>(to));
+// weight gradient of mid 389 -> 430 us.)  Rows that are no multiple of 128
+// bytes cut the pieces across lines, which then leave in parts: plain stores
+// there (128 experts of 700 rows, d = 1000, f = 128 196 -> 174 us a forward).
+template <bool WHOLE>
+__device__ __forceinline__ void store_perm(uint16_t* to, const uint4& v) {
+  if constexpr (WHOLE)
+    __builtin_nontemporal_store(u32x4a{v.x, v.y, v.z, v.w}, reinterpret_cast<u32x4a*>(to));
+  else
+    *reinterpret_cast<uint4*>(to) = v;
 }
 
 __device__ __forceinline__ uint2 pack4(float a, float b, float c, float d) {
@@ -1188,26 +1194,31 @@ __global__ __launch_bounds__(Geom<S>::NTHR, 2) void grouped_gemm_kernel(GemmArgs
           });
         });
         fence();
-        static_for<4>([&](auto Tt) {
-          constexpr int t = Tt;
-          const int r = 8 * t + (lane >> 3), c = lane & 7;
-          const uint4 v = unswap(get16(r * 128 + ((c ^ ((r >> 1) & 7)) << 4)), r);
-          const int rt = rb + r, col = n0 + wn * 64 + 8 * c;
-          // column limit: d; the block's columns (VOC_DW); G's whole pitch,
-          // zeros past the block included (VOC_GRAD)
-          const int climit = MODE == VOC_GRAD ? static_cast<int>(g.c_ld) : DENSE ? g.dN : d;
-          if (rt < mvalid && col < climit) {
-            uint16_t* out;
-            if constexpr (MODE == FWD_DOWN) out = g.y + (int64_t)(seg + m0 + rt) * d;
-            else if constexpr (MODE == DGRAD_GATE_UP) out = g.dx + (int64_t)(seg + m0 + rt) * d;
-            else if constexpr (MODE == WGRAD_DOWN) out = g.dwd + e * wdf + (int64_t)(m0 + rt) * d;
-            else if constexpr (MODE == VOC_GRAD) out = static_cast<uint16_t*>(g.dc) + (int64_t)(m0 + rt) * g.c_ld;
-            else out = static_cast<uint16_t*>(g.dc) + (int64_t)(m0 + rt) * g.c_ld + g.cc0;  // VOC_DW
-            if constexpr (MODE == VOC_DW) store_any(out + col, v, g.dN - col);
-            else if constexpr (MODE == FWD_DOWN || MODE == DGRAD_GATE_UP) store_nt(out + col, v);
-            else *reinterpret_cast<uint4*>(out + col) = v;
-          }
-        });
+        auto write = [&](auto WHOLE) __attribute__((always_inline)) {
+          static_for<4>([&](auto Tt) {
+            constexpr int t = Tt;
+            const int r = 8 * t + (lane >> 3), c = lane & 7;
+            const uint4 v = unswap(get16(r * 128 + ((c ^ ((r >> 1) & 7)) << 4)), r);
+            const int rt = rb + r, col = n0 + wn * 64 + 8 * c;
+            // column limit: d; the block's columns (VOC_DW); G's whole pitch,
+            // zeros past the block included (VOC_GRAD)
+            const int climit = MODE == VOC_GRAD ? static_cast<int>(g.c_ld) : DENSE ? g.dN : d;
+            if (rt < mvalid && col < climit) {
+              uint16_t* out;
+              if constexpr (MODE == FWD_DOWN) out = g.y + (int64_t)(seg + m0 + rt) * d;
+              else if constexpr (MODE == DGRAD_GATE_UP) out = g.dx + (int64_t)(seg + m0 + rt) * d;
+              else if constexpr (MODE == WGRAD_DOWN) out = g.dwd + e * wdf + (int64_t)(m0 + rt) * d;
+              else if constexpr (MODE == VOC_GRAD) out = static_cast<uint16_t*>(g.dc) + (int64_t)(m0 + rt) * g.c_ld;
+              else out = static_cast<uint16_t*>(g.dc) + (int64_t)(m0 + rt) * g.c_ld + g.cc0;  // VOC_DW
+              if constexpr (MODE == VOC_DW) store_any(out + col, v, g.dN - col);
+              else if constexpr (MODE == FWD_DOWN || MODE == DGRAD_GATE_UP) store_perm<WHOLE>(out + col, v);
+              else *reinterpret_cast<uint4*>(out + col) = v;
+            }
+          });
+        };
+        if (MODE != FWD_DOWN && MODE != DGRAD_GATE_UP) write(std::false_type{});
+        else if ((d & 63) == 0) write(std::true_type{});
+        else write(std::false_type{});
         fence();
       }
     });
