@@ -4,6 +4,7 @@
 #include "gemm_kernel.h"
 
 #include <algorithm>
+#include <cmath>
 
 namespace moe {
 using namespace gemm;
@@ -107,16 +108,65 @@ bool use_small(int64_t tiles) {
   const int64_t cus = device_cus();
   return 3 * tiles < 2 * cus * ceil_div(tiles, cus);
 }
-// The forward (its gate/up product up to d = 2048) and the data gradients take
-// it too at 16 rows per expert or fewer on average, where a product is its
-// weights' stream and two workgroups a CU keep more of it in flight (64 experts
-// of 8 rows, d = 2048, f = 1408: down 78 -> 70 us, data gradients 261 -> 201;
-// beyond the line 128 experts of 62 rows, d = 4096: 1043 -> 1194 us a forward).  The weight gradients do not: there they
-// write far more than they read, in pieces half as long (the same 64 experts
-// 306 us against 357, 128 of 8 rows, d = 4096, f = 1536 1107 against 1420).
+// The down product and the data gradients take it too at 16 rows per expert or
+// fewer on average, where a product is its weights' stream and two workgroups a
+// CU keep more of it in flight (64 experts of 8 rows, d = 2048, f = 1408: down
+// 78 -> 70 us, data gradients 261 -> 201; beyond the line 128 experts of 62
+// rows, d = 4096: 1043 -> 1194 us a forward).
 bool few_rows(int64_t rows, int64_t experts) { return rows <= 16 * experts; }
+// The weight gradients of few rows write far more than they read, in pieces
+// half as long on the 128-row tile (the same 64 experts 306 us against 357, 128
+// of 8 rows, d = 4096, f = 1536 1107 against 1420): a tile a quarter as large
+// costs three eighths, which pays where 256-row tiles leave CUs idle (48
+// experts, 96 rows in all, d = 264, f = 328, the backward 52 -> 44 us).  Of 341
+// layers of few rows the down product is more than 4 % off its better tile in
+// 16; by the two-thirds rule alone in 54.
+bool small_weights(int64_t t256, int64_t t128) {
+  const int64_t cus = device_cus();
+  return use_small(t256) || 3 * ceil_div(t128, cus) < 8 * ceil_div(t256, cus);
+}
 // Upper bound of the row tiles of E_loc experts with up to cap rows in all.
 int64_t row_tiles(int64_t cap, int E_loc) { return std::min<int64_t>(cap, E_loc) + cap / TILE; }
+
+// That bound says nothing of a CU that gets two 128-row tiles and its neighbour
+// one, or of tiles that do not exist: 16 experts of 139 rows, d = 2048, f =
+// 1536 have 192 gate/up tiles, counted as 288 (73 us on them, 86 on 768 small
+// ones); 12 of 75, d = 5120 141 against 167; 8 of 83, d = f = 4096 163 against
+// 183.  And the gate/up product's weights lie along f: of few rows per expert,
+// its 128-row tile reads them in pieces half as long, which pays where it fills
+// idle CUs (256- against 128-row tiles: 8 experts of 12 rows, d = 7168, f = 72
+// 86 us against 54, 24 of one row, d = 2560, f = 768 55 against 39) and costs
+// where both fill the chip (128 of 8, d = 4096, f = 1536 585 against 690, 32 of
+// 8, d = 7168, f = 2048 364 against 435).  So these products weigh what their
+// busiest CU does, `rows` rows spread evenly over the experts that get
+// any at random.  A tile costs a fixed part and, per K step, its operands' rows
+// and columns: 1000 + steps (h + 256) for a 256-row tile of h rows; 500 a pair
+// + 0.95 steps (h + 128) for a 128-row tile (a fit to 760 random layers, both
+// tiles measured).
+bool large_cheaper(int64_t rows, int64_t experts, int64_t n256, int64_t n128, int64_t K) {
+  const int64_t cus = device_cus(), ks = ceil_div(K, BK);
+  const double e = static_cast<double>(experts), m = static_cast<double>(rows);
+  rows = std::max<int64_t>(1, rows);
+  const int64_t any = static_cast<int64_t>(std::ceil(-e * std::expm1(-m / e)));
+  const int64_t p = std::max<int64_t>(1, std::min(any, std::min(rows, experts)));
+  const int64_t n = ceil_div(rows, p), m256 = ceil_div(n, TILE), m128 = ceil_div(n, TILE_S);
+  auto height = [&](int64_t mt) { return 32 * std::max<int64_t>(2, ceil_div(n, 32 * mt)); };
+  const int64_t t256 = p * m256 * n256, t128 = p * m128 * n128;
+  return 20 * ceil_div(t256, cus) * (1000 + ks * (height(m256) + 256)) <
+         20 * ceil_div(t128, 2 * cus) * 500 + 19 * ceil_div(t128, cus) * ks * (height(m128) + 128);
+}
+// The host knows the capacity alone, so the 256-row tile has to be the cheaper
+// one at less as well: at a quarter and an eighth of the rows (one rank's share)
+// or, of few rows, on half of the experts (a rank that holds those of its own).
+// A product of fewer tiles than the capacity's would lose more on it (3 experts
+// of 1051 rows of 4206, d = 760, f = 336, a forward 65 -> 89 us) than one of all
+// of them gains.
+bool keep_large(int64_t cap, int E_loc, int64_t n256, int64_t n128, int64_t K) {
+  if (!large_cheaper(cap, E_loc, n256, n128, K)) return false;
+  if (few_rows(cap, E_loc)) return large_cheaper(cap, ceil_div(E_loc, 2), n256, n128, K);
+  return large_cheaper(cap / 4, E_loc, n256, n128, K) &&
+         large_cheaper(cap / 8, E_loc, n256, n128, K);
+}
 
 hipError_t sched(const int32_t* offsets, int E_loc, int rows, int krows, const GemmWs& w,
                  hipStream_t s) {
@@ -144,22 +194,21 @@ hipError_t launch_ffn_fwd(const uint16_t* x_perm, const int32_t* offsets, int E_
   const int64_t rt = row_tiles(cap, E_loc);
   const bool idle = use_small(rt * std::max(ceil_div(f, TILE / 2), ceil_div(d, TILE)));
   const bool few = few_rows(cap, E_loc);
-  // gate/up, down: the gate/up product's weights lie along f, so its 128-row
-  // tile reads them in pieces half as long, which costs more than the second
-  // workgroup brings once its loop over d is long (256- against 128-row tiles:
-  // 128 experts of 8 rows, d = 4096, f = 1536 585 us against 690, 64 of 8, d =
-  // 3072 257 against 298, 32 of 8, d = 7168, f = 2048 364 against 435; d =
-  // 2048 even to 7 % slower, where few experts have rows)
-  const bool small = idle || (few && d <= 2048), small_d = idle || few;
+  // gate/up, down
+  const bool small = (idle || few) &&
+                     !keep_large(cap, E_loc, ceil_div(f, TILE / 2), ceil_div(f, TILE_S / 2), d);
+  const bool small_d =
+      few || (idle && !keep_large(cap, E_loc, ceil_div(d, TILE), ceil_div(d, TILE_S), f));
   int32_t* mt_down = w.mt_start;
-  if (small && E_loc <= REG_EXPERTS) {
+  if (small && small_d && E_loc <= REG_EXPERTS) {
     w.mt_start = mt_down = nullptr;  // the kernels form the tables
   } else {
-    // no product of the forward counts K steps: their table holds the 128-row
-    // tiles where only the down product takes those
+    // no product of the forward counts K steps: their table holds the down
+    // product's row tiles where these are other ones
     const bool both = small != small_d;
     if (both) mt_down = w.wk_start;
-    if (hipError_t e = sched(offsets, E_loc, small ? TILE_S : TILE, both ? TILE_S : BK, w, s);
+    if (hipError_t e = sched(offsets, E_loc, small ? TILE_S : TILE,
+                             !both ? BK : small_d ? TILE_S : TILE, w, s);
         e != hipSuccess)
       return e;
   }
@@ -183,13 +232,19 @@ hipError_t launch_ffn_bwd(const uint16_t* dy, const uint16_t* x_perm, const uint
                           uint16_t* dwd, unsigned flags, void* ws, hipStream_t s) {
   GemmWs w = carve(ws, cap, E_loc, f, true);
   const int64_t rt = row_tiles(cap, E_loc);
+  // the data gradients share one table of row tiles, and so a tile
   const bool small =
-      use_small(rt * std::max(ceil_div(f, TILE), ceil_div(d, TILE))) || few_rows(cap, E_loc);
+      few_rows(cap, E_loc) ||
+      (use_small(rt * std::max(ceil_div(f, TILE), ceil_div(d, TILE))) &&
+       !(keep_large(cap, E_loc, ceil_div(f, TILE), ceil_div(f, TILE_S), d) &&
+         keep_large(cap, E_loc, ceil_div(d, TILE), ceil_div(d, TILE_S), 2 * int64_t{f})));
   const int S = small ? TILE_S : TILE;
   const int64_t experts = std::min<int64_t>(cap, E_loc);
   const bool wgrad = (flags & MOE_BWD_WGRAD) != 0;
-  const bool small_g = use_small(experts * ceil_div(d, TILE) * ceil_div(f, TILE / 2));
-  const bool small_d = use_small(experts * ceil_div(f, TILE) * ceil_div(d, TILE));
+  const bool small_g = small_weights(experts * ceil_div(d, TILE) * ceil_div(f, TILE / 2),
+                                     experts * ceil_div(d, TILE_S) * ceil_div(f, TILE_S / 2));
+  const bool small_d = small_weights(experts * ceil_div(f, TILE) * ceil_div(d, TILE),
+                                     experts * ceil_div(f, TILE_S) * ceil_div(d, TILE_S));
   if (small && (!wgrad || (small_g && small_d)) && E_loc <= REG_EXPERTS)
     w.mt_start = nullptr;  // the kernels form the tables
   else if (hipError_t e = sched(offsets, E_loc, S, BK, w, s); e != hipSuccess)

@@ -3,6 +3,8 @@ compare it with the CPU oracle (full tensors at small sizes, sampled rows,
 tokens and weight-gradient entries at full sizes)."""
 from __future__ import annotations
 
+import math
+
 import numpy as np
 import torch
 
@@ -17,13 +19,49 @@ def bits(t):
     return W.bf16_bits(t)
 
 
-def large_tile(tiles, rows=1, experts=0):
-    """Whether a grouped GEMM launch of `tiles` 256-row tiles (forward and data
-    gradients: of `rows` rows over `experts` experts) runs them, and not
+def large_tile(tiles):
+    """Whether a dense product of `tiles` 256-row tiles runs them, and not
     128-row tiles: the launch's own rule, for tests that cover one or the
     other."""
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    return 3 * tiles >= 2 * cus * -(-tiles // cus) and rows > 16 * experts
+    return 3 * tiles >= 2 * cus * -(-tiles // cus)
+
+
+def large_weights(t256, t128):
+    """Whether a weight gradient of t256 256-row or t128 128-row tiles runs the
+    former: the launch's own rule."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    return large_tile(t256) and 3 * -(-t128 // cus) >= 8 * -(-t256 // cus)
+
+
+def row_tiles(rows, experts, d, f):
+    """The tiles of a forward's gate/up and down product and of the data
+    gradients, by the launches' own rule: "L" (256 rows) or "S" (128) each."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    up = lambda a, b: -(-a // b)  # noqa: E731
+
+    def large_cheaper(m, e, n256, n128, K):
+        any_ = math.ceil(-e * math.expm1(-m / e))
+        m = max(1, m)
+        p = max(1, min(any_, m, e))
+        n, ks = up(m, p), up(K, 64)
+        m256, m128 = up(n, 256), up(n, 128)
+        h = lambda mt: 32 * max(2, up(n, 32 * mt))  # noqa: E731
+        t256, t128 = p * m256 * n256, p * m128 * n128
+        return (20 * up(t256, cus) * (1000 + ks * (h(m256) + 256)) <
+                20 * up(t128, 2 * cus) * 500 + 19 * up(t128, cus) * ks * (h(m128) + 128))
+
+    few = rows <= 16 * experts
+    idle = not large_tile((min(rows, experts) + rows // 256) * max(up(f, 128), up(d, 256)))
+    large = lambda *n: large_cheaper(rows, experts, *n) and (  # noqa: E731
+        large_cheaper(rows, up(experts, 2), *n) if few else
+        large_cheaper(rows // 4, experts, *n) and large_cheaper(rows // 8, experts, *n))
+    small = (idle or few) and not large(up(f, 128), up(f, 64), d)
+    small_d = few or (idle and not large(up(d, 256), up(d, 128), f))
+    dgrad = few or (
+        not large_tile((min(rows, experts) + rows // 256) * max(up(f, 256), up(d, 256))) and
+        not (large(up(f, 256), up(f, 128), d) and large(up(d, 256), up(d, 128), 2 * f)))
+    return "".join("S" if s else "L" for s in (small, small_d, dgrad))
 
 
 def f64(t):

@@ -122,8 +122,8 @@ def test_small_full_parity(name):
         # the kernel's (K steps summed over experts with rows at least 16 per
         # such expert)
         up = lambda a, b: -(-a // b)  # noqa: E731
-        for tiles in (up(wl.d, 256) * up(wl.f, 128), up(wl.f, 256) * up(wl.d, 256)):
-            assert P.large_tile(wl.E * tiles), tiles
+        assert P.large_weights(*(wl.E * up(wl.d, m) * up(wl.f, m // 2) for m in (256, 128)))
+        assert P.large_weights(*(wl.E * up(wl.f, m) * up(wl.d, m) for m in (256, 128)))
         n = np.diff(gpu["expert_offsets"].cpu().numpy().astype(np.int64))
         steps = (n + 63) // 64
         assert steps.sum() >= 16 * (n > 0).sum(), (steps.sum(), (n > 0).sum())

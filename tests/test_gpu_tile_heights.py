@@ -20,33 +20,35 @@ COUNTS = {
     "experts_63": [0] + [(7 * i) % 43 for i in range(62)],
     "experts_64": [(7 * i) % 43 for i in range(63)] + [40],
     "experts_65": [(7 * i) % 43 for i in range(63)] + [0, 300],
-    # few rows an expert: 128-row forward and data gradients beside (f = 5128)
-    # 256-row weight gradients, both sides of the in-register tables
+    # few rows an expert: 128-row data gradients beside (d = 2056) a 256-row
+    # gate/up weight gradient, both sides of the in-register tables
     "few_rows_60": [i % 9 for i in range(60)],
     "few_rows_70": [130] + [i % 9 for i in range(69)],
 }
 
 
-# forward and data gradients on the 128-row tile (few tiles in all), on either,
-# and on the 256-row tile (more than two tiles per compute unit); with few rows
-# an expert and d > 2048 the 256-row gate/up product beside the 128-row down
-# product, whose tile counts differ (an expert of 130 rows)
-@pytest.mark.parametrize("name,d,f", [(n, *df) for df in [(72, 136), (264, 328), (72, 5128)]
-                                      for n in COUNTS] + [("few_rows_60", 2056, 136),
-                                                          ("few_rows_70", 2056, 136)])
-def test_rows_around_tile_heights(name, d, f):
+# the tiles of the forward's gate/up and down products and of the data
+# gradients: the 128-row tile (few tiles in all), the 256-row tile (more than
+# two tiles per compute unit; few rows stay on the 128-row tile), and the two
+# mixed in one pass, where the forward's two tables of row tiles differ
+CASES = [(n, 72, 136, "SSS") for n in COUNTS]
+CASES += [(n, 264, 328, "LLS" if n.startswith("experts") else "SSS") for n in COUNTS]
+CASES += [(n, 72, 5128, "SSS" if n.startswith("few") else "LLL") for n in COUNTS]
+CASES += [("experts_62", 1032, 264, "LSS"), ("experts_63", 1032, 264, "LSS"),
+          ("two_tiles", 2440, 840, "SLS"), ("few_rows_60", 2056, 384, "SSS"),
+          ("few_rows_70", 2056, 384, "SSS")]
+
+
+@pytest.mark.parametrize("name,d,f,tiles", CASES)
+def test_rows_around_tile_heights(name, d, f, tiles):
     from paper_2607_01844_amd import moe
     counts = COUNTS[name]
     print(f"[tile heights] {name} d={d} f={f}", flush=True)
     E, M = len(counts), sum(counts)
     up = lambda a, b: -(-a // b)  # noqa: E731
-    for n in (max(up(f, 128), up(d, 256)), max(up(f, 256), up(d, 256))):  # forward, data gradients
-        if d == 2056:
-            assert M <= 16 * E and P.large_tile((min(M, E) + M // 256) * n)
-        elif f != 328:
-            assert P.large_tile((min(M, E) + M // 256) * n, M, E) == (f == 5128 and M > 16 * E)
-        if M <= 16 * E and f == 5128:  # the weight gradients
-            assert P.large_tile(min(M, E) * up(f, 128)) and P.large_tile(min(M, E) * up(f, 256))
+    assert P.row_tiles(M, E, d, f) == tiles
+    if (d, f) == (2056, 384):  # the gate/up weight gradient
+        assert P.large_weights(*(E * up(d, m) * up(f, m // 2) for m in (256, 128)))
     off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
     gen = torch.Generator().manual_seed(M + d)
     r = lambda *s, std=1.0: (torch.randn(s, generator=gen) * std).to(torch.bfloat16)  # noqa: E731
