@@ -39,48 +39,54 @@ __device__ __forceinline__ void lse_merge(float& m, float& s, float m2, float s2
 }
 
 // W waves per row n: the partial pairs part[n][0..ng) of the caller's blocks
-// of per groups each (the last may have fewer).  One wave merges a block's
-// pairs in order (lane l takes groups l, l + 64, ... ascending, then a fixed
-// xor tree over the lanes); the blocks' pairs then go into the row's running
-// pair (m, s) in order, so the result does not depend on how many blocks a
-// launch takes.  The last launch turns the row's pair into its results:
+// of per groups each (the last may have fewer).  A block's pairs are merged in
+// order (lane l takes groups l, l + 64, ... ascending, then a fixed xor tree
+// over the lanes); the blocks' pairs then go into the row's running pair
+// (m, s) in order, so the result does not depend on how many blocks a launch
+// takes.  A block of fewer than 64 groups takes `sub` lanes of a wave (a power
+// of two, per <= sub): the other lanes would hold empty pairs, which merge
+// without a trace.  The last launch turns the row's pair into its results:
 // lse_n = m_n + log s_n, loss_n = y_{n, t_n} - lse_n.  Bound by latency (loads,
-// then twelve dependent shuffles and exponentials a block): with several
-// blocks four waves share a row, two blocks each at a time (N = 1000, H = 520,
-// V = 32003 in blocks of 4096, loss and gradients: 497 us against 500 with one
-// wave a row, and 499 with the results in a launch of their own).
+// then up to twelve dependent shuffles and exponentials a block): where one
+// wave would come round its 64 / sub blocks often, four waves share a row, 128 /
+// sub blocks each at a time (N = 1000, H = 520, V = 32003 in blocks of 4096,
+// loss and gradients: 497 us against 500 with one wave a row, and 499 with the
+// results in a launch of their own; forward of N = 2048, H = 64, V = 8192 in
+// blocks of 512: 20 us, with sub = 64 27, with sub = 8 but four waves 22).
 template <int W>
 __global__ __launch_bounds__(256) void voc_merge_kernel(const float2* __restrict__ part, int ng,
-                                                        int per, int64_t N, float* __restrict__ m,
+                                                        int per, int sub, int64_t N,
+                                                        float* __restrict__ m,
                                                         float* __restrict__ s, int first, int last,
                                                         const float* __restrict__ yt,
                                                         float* __restrict__ loss,
                                                         float* __restrict__ lse) {
   constexpr int U = W == 1 ? 1 : 2;
-  __shared__ float2 blk[W == 1 ? 1 : U * W];
+  __shared__ float2 blk[W == 1 ? 1 : 64 * U * W];  // a block's pair each
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wv = wave % W;
   const int64_t n = static_cast<int64_t>(blockIdx.x) * (4 / W) + wave / W;
   if (n >= N) return;  // W = 4: the whole workgroup
+  const int nsub = 64 / sub, li = lane & (sub - 1), sl = lane / sub;
+  const int nb = U * W * nsub;  // blocks at a time
   const float2* row = part + n * ng;
   float rm = 0.0f, rs = 0.0f;
   if (!first) {
     rm = m[n];
     rs = s[n];
   }
-  for (int g0 = 0; g0 < ng; g0 += U * W * per) {
+  for (int g0 = 0; g0 < ng; g0 += nb * per) {
     float tm[U], ts[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       tm[u] = -__builtin_huge_valf();
       ts[u] = 0.0f;
-      const int b = g0 + (u * W + wv) * per, e = b + per < ng ? b + per : ng;
-      for (int c = b + lane; c < e; c += 64) {
+      const int b = g0 + ((u * W + wv) * nsub + sl) * per, e = b + per < ng ? b + per : ng;
+      for (int c = b + li; c < e; c += sub) {
         const float2 p = row[c];
         lse_merge(tm[u], ts[u], p.x, p.y);
       }
     }
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
+    for (int o = 1; o < sub; o <<= 1) {
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const float m2 = __shfl_xor(tm[u], o, 64), s2 = __shfl_xor(ts[u], o, 64);
@@ -92,16 +98,22 @@ __global__ __launch_bounds__(256) void voc_merge_kernel(const float2* __restrict
       }
     }
     if constexpr (W == 1) {
-      if (first && g0 == 0) {
-        rm = tm[0];
-        rs = ts[0];
-      } else {
-        lse_merge(rm, rs, tm[0], ts[0]);
+      for (int q = 0; q < nsub && g0 + q * per < ng; ++q) {
+        const float pm = __shfl(tm[0], q * sub, 64), ps = __shfl(ts[0], q * sub, 64);
+        if (first && g0 == 0 && q == 0) {
+          rm = pm;
+          rs = ps;
+        } else {
+          lse_merge(rm, rs, pm, ps);
+        }
       }
     } else {
-      if (lane < U) blk[lane * W + wv] = lane == 0 ? make_float2(tm[0], ts[0]) : make_float2(tm[1], ts[1]);
+      if (li == 0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) blk[(u * W + wv) * nsub + sl] = make_float2(tm[u], ts[u]);
+      }
       __syncthreads();
-      for (int q = 0; q < U * W && g0 + q * per < ng; ++q) {
+      for (int q = 0; q < nb && g0 + q * per < ng; ++q) {
         const float2 p = blk[q];
         if (first && g0 == 0 && q == 0) {
           rm = p.x;
@@ -205,6 +217,15 @@ int64_t fwd_block(int H, int64_t V, int64_t vblock) {
   const int64_t most = max_pitch(std::min(H, 32));
   return staged_fwd(H, V) && std::min(vblock, V) > most ? most : vblock;
 }
+// The block that the forward walks: the caller's, less what is beyond a whole
+// number of groups of 64 columns.  A block that ended inside a group could not
+// be part of a longer product (its columns would fall into other groups, and
+// the pairs be other sums), and had to be a launch of its own: N = 500, H =
+// 520, V = 32000 in blocks of 1000 took 458 us in 32 launches, 35 in one.
+int64_t fwd_step(int H, int64_t V, int64_t vblock) {
+  const int64_t b = fwd_block(H, V, vblock);
+  return b < V && b > 64 ? b / 64 * 64 : b;
+}
 int64_t bwd_block(int64_t N, int H, int64_t V, int64_t vblock) {
   const int64_t rows = std::max<int64_t>(N, staged_bwd(H, V, vblock) ? H : 1);
   const int64_t most = max_pitch(std::min<int64_t>(rows, 256));
@@ -231,13 +252,11 @@ size_t fwd_bytes(int64_t N, int H, int64_t V, int64_t span);
 // set.  One product of many tiles instead of one per block: fewer launches
 // and partly filled last rounds (N = 1000, H = 520, V = 32003 in blocks of
 // 4096: 8 products and merges become 2; N = 4096, H = 2048, V = 200000: 13
-// become 1).  Blocks that do not end on a group of 64 columns stay alone: in a
-// longer product their columns would fall into other groups, and the pairs be
-// other sums.  A copy of W stays within reach and one launch (2^31 threads of
-// eight columns).
+// become 1).  Blocks of fewer than 64 columns stay alone.  A copy of W stays
+// within reach and one launch (2^31 threads of eight columns).
 int64_t fwd_span(int64_t N, int H, int64_t V, int64_t vblock) {
   const size_t room = std::max(vocab_fwd_ws_bytes(N, H, V, vblock), vocab_bwd_ws_bytes(N, H, V, vblock));
-  vblock = fwd_block(H, V, vblock);
+  vblock = fwd_step(H, V, vblock);
   if (vblock % 64 != 0) return vblock;
   int64_t most = std::min<int64_t>(ceil_div(V, vblock), ((int64_t{1} << 40) - 1) / (N * vblock));
   if (staged_fwd(H, V))
@@ -284,10 +303,12 @@ hipError_t launch_vocab_fwd(const uint16_t* x, const uint16_t* w, const int32_t*
   if (N == 0) return hipSuccess;
   // a caller with room for the forward alone gets its blocks one by one
   const int64_t span = ws_bytes >= vocab_bwd_ws_bytes(N, H, V, vblock) ? fwd_span(N, H, V, vblock)
-                                                                         : fwd_block(H, V, vblock);
+                                                                         : fwd_step(H, V, vblock);
   const int64_t vbmax = std::min(span, V);
-  // groups of 64 columns per block of the caller's
-  const int per = static_cast<int>(ceil_div(std::min(fwd_block(H, V, vblock), V), 64));
+  // groups of 64 columns per block
+  const int per = static_cast<int>(ceil_div(std::min(fwd_step(H, V, vblock), V), 64));
+  int sub = 1;
+  while (sub < 64 && sub < per) sub *= 2;
   char* p = static_cast<char*>(ws);
   float* part = reinterpret_cast<float*>(p);
   p += align_up(sizeof(float) * 2 * static_cast<size_t>(N) * ceil_div(vbmax, 64), 256);
@@ -317,12 +338,13 @@ hipError_t launch_vocab_fwd(const uint16_t* x, const uint16_t* w, const int32_t*
     const int ng = static_cast<int>(ceil_div(vb, 64));
     const float2* pairs = reinterpret_cast<const float2*>(part);
     const int first = b0 == 0, last = b0 + span >= V;
-    if (ng <= per || N > (int64_t{1} << 23))  // one block, or rows enough for one wave each
+    const int64_t rounds = ceil_div(ceil_div(ng, per), 64 / sub);  // of one wave a row
+    if (rounds <= (sub < 64 ? 4 : 1) || N > (int64_t{1} << 23))  // or rows enough
       voc_merge_kernel<1><<<static_cast<unsigned>(ceil_div(N, 4)), 256, 0, s>>>(
-          pairs, ng, per, N, m, sm, first, last, yt, loss, lse);
+          pairs, ng, per, sub, N, m, sm, first, last, yt, loss, lse);
     else
-      voc_merge_kernel<4><<<static_cast<unsigned>(N), 256, 0, s>>>(pairs, ng, per, N, m, sm, first,
-                                                                   last, yt, loss, lse);
+      voc_merge_kernel<4><<<static_cast<unsigned>(N), 256, 0, s>>>(pairs, ng, per, sub, N, m, sm,
+                                                                   first, last, yt, loss, lse);
     prof_end(K_VOC_LSE, s);
     if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   }
