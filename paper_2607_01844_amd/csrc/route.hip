@@ -43,7 +43,7 @@ __device__ __forceinline__ void wait_vm() {
 
 // Bound by the fp32 matrix cores where the tiles fill the chip (T = 65536, d =
 // 4096, E = 128: 624 us = 110 TFLOP/s of 157; the vector-ALU chains it replaces
-// took 1365 us; T = 16384, d = 7168, E = 384: 1538 -> 811 us, and 910 on
+// took 1365 us; T = 16384, d = 7168, E = 384: 1538 -> 811 us, and 900 on
 // average among a layer's other kernels), by one wave's chain of d / 4
 // dependent instructions where they do not (T = 1000, d = 4096, E = 128: 95 ->
 // 33 us; T = 16, d = 2048, E = 64: 36 -> 18 us).
